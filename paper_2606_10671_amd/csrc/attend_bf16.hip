@@ -6,9 +6,8 @@
 // Sec. 4.1: the chunk attends over the memory entries plus its own frames).
 //
 // Design (workgroup = 8 waves x 32 queries of one head, one workgroup per
-// CU, two waves per SIMD; the steady-state loop keeps every value in the 256
-// architectural VGPRs of a wave, while the last tiles and the epilogue
-// spill):
+// CU, two waves per SIMD; every value of a wave stays in its 256
+// architectural VGPRs, nothing spills):
 // * The 256 queries of a workgroup share each K/V tile, which is streamed
 //   from L2 into LDS once for all of them.
 // * Transposed scores: S^T = K Q^T puts 16 keys of ONE query in each
@@ -46,9 +45,17 @@
 //   beside the MFMAs than summing the rounded pair with a v_dot2.
 // * Workgroup index -> work is remapped so that one XCD runs a contiguous
 //   range of (head, query tile) and shares K/V in its L2.
+// * A call's time is the loop's, about 1.8 us per key tile and workgroup with
+//   all CUs busy (D = 128), plus what a segment costs once: launch, entry
+//   table, first loads, and the first pass through code that is not yet in
+//   the instruction cache.  So the last tiles share one copy of their code:
+//   256 workgroups over 1 / 4 / 16 key tiles take 14.5 / 19.1 / 41.6 us, with
+//   a copy per ring slot (and its 95 spilled VGPRs) 20.5 / 29.9 / 50.2 us;
+//   12 heads x 4680 queries over 37440 keys 954 against 973 us in one run.
 // * In a head's last query tile, usually partial, the waves whose 32
 //   queries all lie past the last one only issue their share of the tile
 //   loads and meet the barriers: no MFMAs, no softmax, no result.
+#include <algorithm>
 #include <mutex>
 #include <type_traits>
 
@@ -58,26 +65,25 @@ namespace fademem {
 
 // Work split over G resident workgroups.  Query tiles are numbered
 // qg = head * q_tiles + tile within the head, Q of them.  The first
-// rounds*G tiles run whole, round k giving tile k*G + g to group g.  Of the
-// rem = Q - rounds*G remaining tiles, tile i's keys [0, head_len) go to
-// group i (i < rem) and its tail [head_len, tiles) to group
-// rem + i / tails_per: the G - rem tail groups each take tails_per
-// consecutive tails.  head_len = tiles - tail_len, tail_len =
-// (tiles - o (tails_per - 1)) / (tails_per + 1) with o = kSegOverhead key
-// tiles per extra segment, so a tail group's tails_per tails, with their
-// segment overheads, are no more work than one head part.  Every group starts its parts at the same key
-// tile at the same time, so the groups of one XCD read the same K/V tiles
-// together and those come from its L2.  A split tile leaves its head part
-// in scratch slot i and its tail in slot rem + i; a second kernel merges
-// the two.
+// rounds*G tiles run whole, round k giving tile k*G + g to group g.  Each of
+// the rem = Q - rounds*G remaining tiles is cut along the key axis into
+// `heads_per` head parts of about equal length, keys [0, head_len), and one
+// tail [head_len, tiles): head part j of tile i goes to group j * rem + i,
+// tail i to group heads_per * rem + i / tails_per, so the groups left over
+// each take tails_per consecutive tails.  Every head part j starts at the
+// same key tile at the same time, so the groups of one XCD read the same K/V
+// tiles together and those come from its L2.  A split tile leaves each head
+// part in scratch slot j * rem + i and its tail in slot heads_per * rem + i;
+// a second kernel merges them.
 struct SkPlan {
   int tiles;      // key tiles per query tile
   int q_tiles;    // query tiles per head
   int groups;     // G
   int rounds;     // whole rounds
   int rem;        // query tiles left after the whole rounds, < G
-  int head_len;   // key tiles of a remaining tile's head part
-  int tail_len;   // key tiles of its tail part (0: remaining tiles run whole)
+  int heads_per;  // head parts of a remaining tile
+  int head_len;   // key tiles of a remaining tile's head parts together
+  int tail_len;   // key tiles of its tail part (0: no tail)
   int tails_per;  // tails per tail group
 };
 
@@ -101,6 +107,10 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleBound = 256.0f;  // redo a tile whose weights exceed 2^8
 constexpr int kSegOverhead = 2;          // key tiles' worth of time a segment's prologue and epilogue cost
+constexpr int kMinSplit = 10;            // key tiles a query tile needs to be split at all
+constexpr int kMinPart = 6;              // key tiles of a head part at least
+constexpr int kMinTailSaves = 2;         // key tiles a tail has to take off each head part
+constexpr int kMaxParts = 64;            // head parts of a query tile at most
 static_assert(QB * 32 == kQW && (QB == 1 || QB == 2), "32-query blocks per wave");
 
 template <int D>
@@ -158,28 +168,37 @@ __device__ __forceinline__ int xcd_group(int bid, int groups) {
   return (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
-// Final output of one lane for one 32-query block: O row (query q_row,
-// head h) from the O^T accumulators divided by the row sum, and the row's
-// LSE.
+// One lane's part of 32-row block db of O^T (query q_row, head h), scaled by
+// inv, into its O row.
+template <int D>
+__device__ __forceinline__ void store_block(const AttendArgs& args, const f32x16& o, int db, float inv, int q_row,
+                                            int h, int hh) {
+  if (q_row >= int(args.q_tokens)) return;
+  char* obase = static_cast<char*>(args.out) + (size_t(q_row) * args.heads + h) * D * 2;
+#pragma unroll
+  for (int g4 = 0; g4 < 4; ++g4) {
+    bf16x4 v;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) v[r] = (__bf16)(o[4 * g4 + r] * inv);
+    const int d = 32 * db + 8 * g4 + 4 * hh;
+    *reinterpret_cast<bf16x4*>(obase + d * 2) = v;
+  }
+}
+// The row's log-sum-exp, if asked for.
+__device__ __forceinline__ void store_lse(const AttendArgs& args, float m_scaled, float l_tot, int q_row, int h,
+                                          int hh) {
+  if (args.lse && hh == 0 && q_row < int(args.q_tokens))
+    args.lse[size_t(h) * args.q_tokens + q_row] = (m_scaled + __log2f(l_tot)) * kLn2;
+}
+// Final output of one lane for one 32-query block: its O row from the O^T
+// accumulators divided by the row sum, and the row's LSE.
 template <int D>
 __device__ __forceinline__ void store_out(const AttendArgs& args, const f32x16 (&o)[Shape<D>::DB], float m_scaled,
                                           float l_tot, int q_row, int h, int hh) {
-  const int H = args.heads;
-  const int Lq = int(args.q_tokens);
-  if (q_row >= Lq) return;
   const float inv = 1.0f / l_tot;
-  char* obase = static_cast<char*>(args.out) + (size_t(q_row) * H + h) * D * 2;
 #pragma unroll
-  for (int db = 0; db < Shape<D>::DB; ++db)
-#pragma unroll
-    for (int g4 = 0; g4 < 4; ++g4) {
-      bf16x4 v;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) v[r] = (__bf16)(o[db][4 * g4 + r] * inv);
-      const int d = 32 * db + 8 * g4 + 4 * hh;
-      *reinterpret_cast<bf16x4*>(obase + d * 2) = v;
-    }
-  if (args.lse && hh == 0) args.lse[size_t(h) * Lq + q_row] = (m_scaled + __log2f(l_tot)) * kLn2;
+  for (int db = 0; db < Shape<D>::DB; ++db) store_block<D>(args, o[db], db, inv, q_row, h, hh);
+  store_lse(args, m_scaled, l_tot, q_row, h, hh);
 }
 
 // Scratch slot layout of a partial result: O registers lane-major,
@@ -566,15 +585,14 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
     constexpr int kDbPerStep = S::DB * 4 / kStepsB;   // = 2
     constexpr int kPrefetch = 1;                      // steps between an LDS read and its MFMA
 
-    // One pipeline iteration for tile t (ring slot b): boundary, block A,
-    // tile t's weight check, block B.  LOAD: tile t+2 exists (its loads are
-    // issued); NEXT: tile t+1 exists; maskn: tile t+1 has keys >= Lk.
-    auto iteration = [&](int t, auto b_c, auto load_c, auto next_c, bool maskn) {
-      constexpr int b = decltype(b_c)::value;
+    // One pipeline iteration for tile t: boundary, block A, tile t's weight
+    // check, block B.  kb_cur, vb_cur: tile t's buffers; kb_next: tile t+1's K;
+    // kb_load, vb_load: the free buffers, for tile t+2.  LOAD: tile t+2 exists
+    // (its loads are issued); NEXT: tile t+1 exists; maskn: it has keys >= Lk.
+    auto iteration = [&](int t, const char* kb_cur, const char* vb_cur, const char* kb_next, char* kb_load,
+                         char* vb_load, auto load_c, auto next_c, bool maskn) {
       constexpr bool LOAD = decltype(load_c)::value;
       constexpr bool NEXT = decltype(next_c)::value;
-      const char* kb_next = kbuf[(b + 1) % 3];
-      const char* vb_cur = vbuf[b];
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();  // tiles t, t+1 landed for every wave; tile t-1's buffers are free
       TileRows tr;
@@ -612,7 +630,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
           }
         }
         if constexpr (LOAD) {
-          if (st == 0) load_tile(tr, kbuf[(b + 2) % 3], vbuf[(b + 2) % 3]);
+          if (st == 0) load_tile(tr, kb_load, vb_load);
         }
         if constexpr (NEXT) {
 #pragma unroll
@@ -627,7 +645,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
           if (st == (pi - kPairsB) * S::KB / (kPairs - kPairsB)) exp_pair(s_cur, p_cur, ps_cur, pi);
         __builtin_amdgcn_sched_barrier(0);
       }
-      close_tile(t, kbuf[b], p_cur, ps_cur);  // tile t's K buffer is refilled only in the next block A
+      close_tile(t, kb_cur, p_cur, ps_cur);  // tile t's K buffer is refilled only in the next block A
       __builtin_amdgcn_sched_barrier(0);
 
       // Block B: O += V(t) P(t), two 32-row blocks of one k-step per step,
@@ -692,38 +710,36 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
       for (int pi = 0; pi < kPairsB; ++pi) exp_pair(s_cur, p_cur, ps_cur, pi);
     }
 
-    using I0 = std::integral_constant<int, 0>;
-    using I1 = std::integral_constant<int, 1>;
-    using I2 = std::integral_constant<int, 2>;
+    // Tile t = kt0 + i uses ring slot i % 3.
     using T = std::true_type;
     using F = std::false_type;
-    int t = kt0;
-    while (true) {
-      if (t + 2 >= kt1) break;
-      iteration(t, I0{}, T{}, T{}, false);
+    int t = kt0, b = 0;
+    while (t + 2 < kt1) {
+      iteration(t, kbuf[0], vbuf[0], kbuf[1], kbuf[2], vbuf[2], T{}, T{}, false);
       ++t;
+      b = 1;
       if (t + 2 >= kt1) break;
-      iteration(t, I1{}, T{}, T{}, false);
+      iteration(t, kbuf[1], vbuf[1], kbuf[2], kbuf[0], vbuf[0], T{}, T{}, false);
       ++t;
+      b = 2;
       if (t + 2 >= kt1) break;
-      iteration(t, I2{}, T{}, T{}, false);
+      iteration(t, kbuf[2], vbuf[2], kbuf[0], kbuf[1], vbuf[1], T{}, T{}, false);
       ++t;
+      b = 0;
     }
-    // The last one or two tiles (no loads left to issue).
+    // The last one or two tiles (no loads left to issue).  One copy of each
+    // iteration serves all ring slots, through selected buffer addresses: no
+    // loads are in flight here that the compiler would have to tell apart,
+    // and three copies of each cost more to fetch into the instruction cache
+    // (and 95 spilled VGPRs) than the selects.
+    auto slot_of = [&](char* const (&buf)[3], int i) -> const char* { return i == 0 ? buf[0] : i == 1 ? buf[1] : buf[2]; };
     if (t + 1 < kt1) {
-      const int b = (t - kt0) % 3;
-      const bool mk = (t + 1 == partial_tile);
-      if (b == 0) iteration(t, I0{}, F{}, T{}, mk);
-      else if (b == 1) iteration(t, I1{}, F{}, T{}, mk);
-      else iteration(t, I2{}, F{}, T{}, mk);
+      const int n = b == 2 ? 0 : b + 1;
+      iteration(t, slot_of(kbuf, b), slot_of(vbuf, b), slot_of(kbuf, n), nullptr, nullptr, F{}, T{}, t + 1 == partial_tile);
       ++t;
+      b = n;
     }
-    {
-      const int b = (t - kt0) % 3;
-      if (b == 0) iteration(t, I0{}, F{}, F{}, false);
-      else if (b == 1) iteration(t, I1{}, F{}, F{}, false);
-      else iteration(t, I2{}, F{}, F{}, false);
-    }
+    iteration(t, slot_of(kbuf, b), slot_of(vbuf, b), nullptr, nullptr, nullptr, F{}, F{}, false);
     // (The last tile's rescale was applied at its boundary.)
     if (slot < 0) {
 #pragma unroll
@@ -743,11 +759,12 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
     }
   };
 
-  // The group's parts: its whole tiles, then its head part or its tails.
+  // The group's parts: its whole tiles, then a head part or its tails.
   const int base = plan.rounds * plan.groups;
-  const int i0 = (g - plan.rem) * plan.tails_per;  // first tail (tail groups)
+  const int head_groups = plan.heads_per * plan.rem;
+  const int i0 = (g - head_groups) * plan.tails_per;  // first tail (tail groups)
   int parts = plan.rounds;
-  if (g < plan.rem) {
+  if (g < head_groups) {
     parts += 1;
   } else if (plan.tail_len > 0 && i0 < plan.rem) {
     parts += (i0 + plan.tails_per < plan.rem ? plan.tails_per : plan.rem - i0);
@@ -756,60 +773,78 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
     int qg, kt0 = 0, kt1 = plan.tiles, slot = -1;
     if (part < plan.rounds) {
       qg = part * plan.groups + g;
-    } else if (g < plan.rem) {
-      qg = base + g;
-      kt1 = plan.head_len;
-      slot = plan.tail_len > 0 ? g : -1;
+    } else if (g < head_groups) {
+      const int j = g / plan.rem;
+      qg = base + g - j * plan.rem;
+      kt0 = j * plan.head_len / plan.heads_per;
+      kt1 = (j + 1) * plan.head_len / plan.heads_per;
+      slot = plan.heads_per > 1 || plan.tail_len > 0 ? g : -1;
     } else {
       const int i = i0 + part - plan.rounds;
       qg = base + i;
       kt0 = plan.head_len;
-      slot = plan.rem + i;
+      slot = head_groups + i;
     }
     segment(qg / plan.q_tiles, qg % plan.q_tiles, kt0, kt1, slot);
   }
 }
 
-// Merge of split query tiles: block i combines remaining tile i's head part
-// (slot i) and tail part (slot rem + i) and writes the output.  The slot
-// rows of waves past the last query hold no result; they are read but
-// never stored.
-template <int D>
+// Merge of split query tiles: block (i, w) combines the parts of remaining
+// tile i for the 32 queries of wave w, wave db of the block taking the
+// 32-row block db of O^T, and writes the output.  Bound by the latency of
+// reading the partials (from L2 and the Infinity Cache); eight small blocks
+// per tile fill the chip when few tiles are split (24 tiles of 2 parts 9.2 us
+// as one block per tile, 24 tiles of 10 parts 8.5 us so).  TWO: every tile
+// has two parts, whose loads are then all in flight at once.
+template <int D, bool TWO>
 __device__ __forceinline__ void attend_bf16_merge_body(const AttendArgs& args, const SkPlan& plan) {
-  using S = Shape<D>;
-  const int i = blockIdx.x;
+  static_assert(QB == 1, "one 32-query block per wave");
+  const int i = blockIdx.x, wave = blockIdx.y;
   const int qg = plan.rounds * plan.groups + i;
-  const int tid = threadIdx.x;
-  const int wave = tid >> 6;
-  const int lane = tid & 63;
-  const int l32 = lane & 31;
+  const int db = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
   const int hh = lane >> 5;
+  const int q0 = (qg % plan.q_tiles) * kBM + wave * kQW;
+  if (q0 >= int(args.q_tokens)) return;  // the wave left no result
   const float c2 = args.scale * kLog2e;
-  const float* part[2] = {args.ws + size_t(i) * attend_slot_floats(D),
-                          args.ws + size_t(plan.rem + i) * attend_slot_floats(D)};
+  const int mi = kBM * D + wave * 64 + lane, li = mi + kThreads;
+  const float* base = args.ws + size_t(i) * attend_slot_floats(D);
+  const size_t step = size_t(plan.rem) * attend_slot_floats(D);  // from one part of the tile to its next
+  f32x16 o;
+  float m_max, l_tot;
+  if constexpr (TWO) {
+    const float* other = base + step;
+    f32x16 o1;
 #pragma unroll
-  for (int qb = 0; qb < QB; ++qb) {
-    const int mi = kBM * D + qb * kThreads + tid, li = kBM * D + (QB + qb) * kThreads + tid;
-    const float m_max = fmaxf(part[0][mi], part[1][mi]);
-    f32x16 o[S::DB];
+    for (int r = 0; r < 16; ++r) {
+      o[r] = base[ws_o_index<D>(wave, 0, db, r, lane)];
+      o1[r] = other[ws_o_index<D>(wave, 0, db, r, lane)];
+    }
+    const float m0 = base[mi], m1 = other[mi];
+    m_max = fmaxf(m0, m1);
+    const float f0 = __builtin_amdgcn_exp2f((m0 - m_max) * c2), f1 = __builtin_amdgcn_exp2f((m1 - m_max) * c2);
+    l_tot = f0 * pair_sum(base[li]) + f1 * pair_sum(other[li]);
 #pragma unroll
-    for (int db = 0; db < S::DB; ++db)
+    for (int r = 0; r < 16; ++r) o[r] = f0 * o[r] + f1 * o1[r];
+  } else {
+    const int parts = plan.heads_per + (plan.tail_len > 0 ? 1 : 0);
+    m_max = base[mi];
+#pragma unroll 4
+    for (int p = 1; p < parts; ++p) m_max = fmaxf(m_max, base[p * step + mi]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[db][r] = 0.0f;
-    float l_tot = 0.0f;
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const float* ws = part[p];
+    for (int r = 0; r < 16; ++r) o[r] = 0.0f;
+    l_tot = 0.0f;
+#pragma unroll 4
+    for (int p = 0; p < parts; ++p) {
+      const float* ws = base + p * step;
       const float f = __builtin_amdgcn_exp2f((ws[mi] - m_max) * c2);
       l_tot += f * pair_sum(ws[li]);
 #pragma unroll
-      for (int db = 0; db < S::DB; ++db)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[db][r] += f * ws[ws_o_index<D>(wave, qb, db, r, lane)];
+      for (int r = 0; r < 16; ++r) o[r] += f * ws[ws_o_index<D>(wave, 0, db, r, lane)];
     }
-    store_out<D>(args, o, m_max * c2, l_tot, (qg % plan.q_tiles) * kBM + wave * kQW + 32 * qb + l32,
-                 qg / plan.q_tiles, hh);
   }
+  store_block<D>(args, o, db, 1.0f / l_tot, q0 + (lane & 31), qg / plan.q_tiles, hh);
+  if (db == 0) store_lse(args, m_max * c2, l_tot, q0 + (lane & 31), qg / plan.q_tiles, hh);
 }
 
 }  // namespace
@@ -827,19 +862,17 @@ __global__ __launch_bounds__(kThreads, 1) void attend_bf16_d128_short(AttendArgs
 __global__ __launch_bounds__(kThreads, 1) void attend_bf16_d64_short(AttendArgs args, SkPlan plan) {
   attend_bf16_body<64, false>(args, plan);
 }
-__global__ __launch_bounds__(kThreads) void attend_bf16_merge_d128(AttendArgs args, SkPlan plan) {
-  attend_bf16_merge_body<128>(args, plan);
-}
-__global__ __launch_bounds__(kThreads) void attend_bf16_merge_d64(AttendArgs args, SkPlan plan) {
-  attend_bf16_merge_body<64>(args, plan);
+template <int D, bool TWO>
+__global__ __launch_bounds__(2 * D) void attend_bf16_merge(AttendArgs args, SkPlan plan) {
+  attend_bf16_merge_body<D, TWO>(args, plan);
 }
 
 namespace {
 
 typedef void (*AttnKernel)(AttendArgs, SkPlan);
 
-hipError_t launch_d(AttnKernel kernel, AttnKernel merge, std::once_flag& attr_once, const AttendArgs& a,
-                    hipStream_t stream) {
+hipError_t launch_d(AttnKernel kernel, AttnKernel merge2, AttnKernel merge_n, std::once_flag& attr_once,
+                    const AttendArgs& a, hipStream_t stream) {
   const int64_t q_tiles64 = (a.q_tokens + kBM - 1) / kBM;
   if (q_tiles64 * a.heads > int64_t(0x7fffffff)) return hipErrorInvalidValue;
   const int64_t lk = a.n_entries * a.tokens_per_block + a.cur_tokens;
@@ -866,22 +899,45 @@ hipError_t launch_d(AttnKernel kernel, AttnKernel merge, std::once_flag& attr_on
   plan.groups = int(groups);
   plan.rounds = total / plan.groups;
   plan.rem = total - plan.rounds * plan.groups;
-  plan.tails_per = plan.rem > 0 ? (plan.rem + (plan.groups - plan.rem) - 1) / (plan.groups - plan.rem) : 1;
-  {
-    // A tail group runs tails_per segments, each with a prologue (two tile
-    // loads waited in full) and an epilogue: about kSegOverhead key tiles
-    // each, beyond the head part's one.
-    const int over = kSegOverhead * (plan.tails_per - 1);
-    plan.tail_len = plan.tiles > over ? (plan.tiles - over) / (plan.tails_per + 1) : 0;
+  plan.heads_per = 1;
+  plan.tails_per = 1;
+  plan.tail_len = 0;
+  if (plan.rem > 0 && plan.tiles >= kMinSplit) {
+    // Splitting pays once the key tiles it saves outweigh the merge launch
+    // (about 5 us, a key tile 1.2-1.8 us).  Head parts: as many as the groups
+    // allow, none shorter than kMinPart tiles (one segment costs 10-13 us
+    // before its first tile is done, however short): 12 heads x 390 queries
+    // over 61 tiles 27.3 us with 10 parts against 64.0 us with the two of a
+    // head part and a tail; minimum parts of 2, 3, 4 and 6 tiles measure the
+    // same at most sizes, 6 is 5% faster where 3 x 200 queries meet 29 tiles.
+    const int fit = plan.groups / plan.rem, most = plan.tiles / kMinPart;
+    plan.heads_per = std::max(1, std::min(std::min(fit, most), kMaxParts));
+    // Tails for the groups left over.  A tail group runs tails_per segments,
+    // each with a prologue (two tile loads waited in full) and an epilogue:
+    // about kSegOverhead key tiles each, beyond a head part's one.  Its tails
+    // and overheads together are to be no more work than one head part.
+    // Tails that take less than two tiles off every head part are not worth
+    // their slots: 12 heads x 1170 queries over 92 tiles (16 groups left for
+    // 60 tails) 53.5 us without tails, 59.6 us with.
+    const int left = plan.groups - plan.heads_per * plan.rem;
+    if (left > 0) {
+      plan.tails_per = (plan.rem + left - 1) / left;
+      const int over = kSegOverhead * (plan.tails_per - 1) * plan.heads_per;
+      const int len = plan.tiles > over ? (plan.tiles - over) / (plan.tails_per * plan.heads_per + 1) : 0;
+      if (len >= kMinTailSaves * plan.heads_per) plan.tail_len = len;
+    }
   }
   plan.head_len = plan.tiles - plan.tail_len;
-  const int launched =
-      plan.rounds > 0 ? plan.groups
-                      : plan.rem + (plan.tail_len > 0 ? (plan.rem + plan.tails_per - 1) / plan.tails_per : 0);
+  const int launched = plan.rounds > 0
+                           ? plan.groups
+                           : plan.heads_per * plan.rem +
+                                 (plan.tail_len > 0 ? (plan.rem + plan.tails_per - 1) / plan.tails_per : 0);
   hipLaunchKernelGGL(kernel, dim3(launched), dim3(kThreads), shmem, stream, a, plan);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if (plan.rem > 0 && plan.tail_len > 0) {
-    hipLaunchKernelGGL(merge, dim3(plan.rem), dim3(kThreads), 0, stream, a, plan);
+  const int parts = plan.heads_per + (plan.tail_len > 0 ? 1 : 0);
+  if (plan.rem > 0 && parts > 1) {
+    hipLaunchKernelGGL(parts == 2 ? merge2 : merge_n, dim3(plan.rem, kWaves), dim3(2 * a.head_dim), 0, stream, a,
+                       plan);
     e = hipGetLastError();
   }
   return e;
@@ -895,8 +951,10 @@ hipError_t launch_attend_bf16(const AttendArgs& a, hipStream_t stream) {
   const int w = a.tokens_per_block >= kBN ? 1 : 0;
   static const AttnKernel k128[2] = {attend_bf16_d128_short, attend_bf16_d128};
   static const AttnKernel k64[2] = {attend_bf16_d64_short, attend_bf16_d64};
-  if (a.head_dim == 128) return launch_d(k128[w], attend_bf16_merge_d128, attr_once[w], a, stream);
-  if (a.head_dim == 64) return launch_d(k64[w], attend_bf16_merge_d64, attr_once[2 + w], a, stream);
+  if (a.head_dim == 128)
+    return launch_d(k128[w], attend_bf16_merge<128, true>, attend_bf16_merge<128, false>, attr_once[w], a, stream);
+  if (a.head_dim == 64)
+    return launch_d(k64[w], attend_bf16_merge<64, true>, attend_bf16_merge<64, false>, attr_once[2 + w], a, stream);
   return hipErrorInvalidValue;
 }
 

@@ -22,8 +22,9 @@ constexpr int64_t kMaxTokens = int64_t(1) << 30;
 // rounds of resident workgroups, the remaining tiles are split along the key
 // axis between workgroups, each part leaves its partial result (unnormalised
 // O, row max and row sums) in a scratch slot, and a second kernel merges the
-// two parts of each split tile.  At most kSkMaxGroups workgroups per launch,
-// two scratch slots per workgroup.
+// parts of each split tile.  At most kSkMaxGroups workgroups per launch; a
+// workgroup leaves at most one head part or, of the fewer than kSkMaxGroups
+// split tiles, tails: two scratch slots per workgroup cover both.
 constexpr int kAttnThreads = 512;        // threads per workgroup (8 waves)
 constexpr int kAttnQueries = 256;        // queries per workgroup (32 per wave)
 constexpr int kSkMaxGroups = 256;        // workgroups of one launch at most (one per CU)
