@@ -11,20 +11,20 @@
 //   sqrt(1/N), s_k = sqrt(2/N), in fp64, stored fp32;
 // * band_order_kernel -- the coefficients grouped by band (a stable
 //   counting sort in one block), so each band is a contiguous index list;
-// * spectral_fused_kernel (frames up to 64 x 128) -- persistent blocks, each
-//   taking an equal contiguous range of the (clip, lag) frames: per frame
-//   T = z A_W^T and D = A_H T on the fp32 matrix cores
-//   (v_mfma_f32_16x16x4_f32; wave j owns the 16 columns v of tile j), the
-//   second product taking T straight from the first one's accumulators,
-//   then D written to LDS in band order and reduced per band to the fp64
-//   sums S_y, S_yy and S_xy against frame 0's coefficients x (kept in LDS).
-//   Frames go in pairs: both transforms are staged, then one band pass
-//   sums both (six sums per band), so the band pass's latency is paid once
-//   per two frames; no transform ever reaches HBM;
+// * spectral_fused_kernel (frames of up to 128 x 128 whose LDS fits) --
+//   persistent blocks, each taking an equal contiguous range of the
+//   (clip, lag) frames: per frame T = z A_W^T and D = A_H T on the fp32
+//   matrix cores (v_mfma_f32_16x16x4_f32), on the frame folded into its four
+//   even/odd quadrants (half the products in each direction), the second
+//   product taking T straight from the first one's accumulators, then D
+//   written to LDS in band order and reduced per band to the fp64 sums S_y,
+//   S_yy and S_xy against frame 0's coefficients x (kept in LDS); no
+//   transform ever reaches HBM;
 // * clip_mean_kernel -- per clip the Pearson coefficient from those sums
 //   (frame 0's own, at lag 0, give S_x and S_xx), then the mean over clips
 //   in a fixed order (every call gives the same bits).
-// Larger frames take the general path:
+// Frames too large for that (more than 128 rows or columns, or their LDS)
+// take the general path:
 // * dct2_kernel -- one block per (clip, run of frames): both bases (as
 //   transposes) in LDS once, then per frame z^T in LDS, T = z A_W^T and
 //   D = A_H T, each thread computing 4 x 4 output tiles from 16-byte LDS
@@ -37,6 +37,7 @@
 #include <string.h>
 
 #include <mutex>
+#include <type_traits>
 #include <vector>
 
 #include "fademem_internal.h"
@@ -249,32 +250,40 @@ __global__ __launch_bounds__(256) void band_corr_kernel(const float* D, int nlag
   }
 }
 
-// ---- fused path: frames of up to 64 x 128 ------------------------------
-constexpr int kFusedThreads = 512;  // 8 waves; wave j owns v-tile j (16 columns)
-constexpr int kFusedMaxH = 64, kFusedMaxW = 128;
+// ---- fused path: frames of up to 128 x 128 whose LDS fits ----------------
+constexpr int kFusedThreads = 512;  // 8 waves
+constexpr int kFusedMaxH = 128, kFusedMaxW = 128;
 
-__host__ __device__ inline int fused_zl_stride(int W) { return (W + 15) / 16 * 16 + 4; }
+// The DCT's symmetry, A_N[k][N-1-n] = (-1)^k A_N[k][n], halves both products
+// in each direction: with the frame folded into four quadrants (sums and
+// differences of its mirrored rows and columns, by row parity pr and column
+// parity pc), coefficients (2u' + pr, 2v' + pc) need quadrant (pr, pc) alone:
+//   T[h'][v'] = sum_w' Z[h'][w'] A_W[2v' + pc][w'],
+//   D[2u' + pr][2v' + pc] = sum_h' A_H[2u' + pr][h'] T[h'][v'].
+// The middle row (column) of an odd size is its own mirror: it enters the
+// even quadrant once and the odd one as x - x, whose basis value is 0 (so a
+// NaN or infinity there still reaches every coefficient).
+__host__ __device__ inline int half_up(int n) { return (n + 1) / 2; }
 __host__ __device__ inline int r16(int x) { return (x + 15) / 16 * 16; }
+// Row stride of a quadrant in floats: an odd multiple of 4, so the 16-byte
+// reads of 16 consecutive rows, and the 4-byte ones of 16 rows x 4 columns,
+// fall in distinct banks.
+__host__ __device__ inline int fused_stride(int W) { return 4 * (((half_up(W) + 3) / 4) | 1); }
+__host__ __device__ inline int fused_ht(int H) { return (half_up(H) + 15) / 16; }  // row tiles of a quadrant
 
-// Byte offsets of the fused kernel's LDS regions.  zl: the frame, [16 HT]
-// rows of stride S = 16 n + 4 floats (zero outside H x W), so that the
-// 16-byte reads of 16 consecutive rows fall in distinct banks; dl: the
-// transform D in band order (at set-up, the inverse of the band order);
-// dl2: the second frame of a pair;
-// xl: frame 0's coefficients in band order; ahl: A_H as the second
-// product's A fragments; sl: the band starts.
+// Byte offsets of the fused kernel's LDS regions.  zl: the folded frame, four
+// quadrants of 16 HT rows (zero outside H x W); dl: the transform D in band
+// order (at set-up, the inverse of the band order); xl: frame 0's
+// coefficients in band order; sl: the band starts.
 struct FusedLds {
-  int zl, dl, dl2, xl, ahl, sl, total;
+  int zl, dl, xl, sl, total;
 };
 __host__ __device__ inline FusedLds fused_lds(int H, int W, int bands) {
-  const int HT = (H + 15) / 16;
   FusedLds L;
   int off = 0;
-  L.zl = off;  off += r16(16 * HT * fused_zl_stride(W) * 4);
+  L.zl = off;  off += r16(4 * 16 * fused_ht(H) * fused_stride(W) * 4);
   L.dl = off;  off += r16(H * W * 4 + 4);  // + a spare slot that takes left-out coefficients
-  L.dl2 = off; off += r16(H * W * 4 + 4);  // the second frame of a pair
   L.xl = off;  off += r16(H * W * 4);
-  L.ahl = off; off += r16(HT * HT * 256 * 4);
   L.sl = off;  off += r16((bands + 1) * 4);
   L.total = off;
   return L;
@@ -292,84 +301,132 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_update_dpp(0, int(b >> 32), CTRL, 0xf, 0xf, false);
   return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
 }
-__device__ __forceinline__ double lane_f64(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane(int(b), l), hi = __builtin_amdgcn_readlane(int(b >> 32), l);
-  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned int>(lo));
+__device__ __forceinline__ double f64_of(unsigned lo, unsigned hi) {
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | lo);
 }
-// Sum over the 64 lanes in a fixed order (every lane gets the same bits):
-// pairs, quads, eights and sixteens within each row, then the four rows.
-__device__ __forceinline__ double wave_total(double v) {
+// Lanes 0-31: a[l] + a[l + 32]; lanes 32-63: b[l - 32] + b[l].
+__device__ __forceinline__ double fold32(double a, double b) {
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane32_swap(unsigned(x), unsigned(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(unsigned(x >> 32), unsigned(y >> 32), false, false);
+  return f64_of(lo[0], hi[0]) + f64_of(lo[1], hi[1]);
+}
+// Rows of 16 lanes: rows 0 and 2 get a's rows 0 + 1 and 2 + 3, rows 1 and 3 b's.
+__device__ __forceinline__ double fold16(double a, double b) {
+  const long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+  const auto lo = __builtin_amdgcn_permlane16_swap(unsigned(x), unsigned(y), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(unsigned(x >> 32), unsigned(y >> 32), false, false);
+  return f64_of(lo[0], hi[0]) + f64_of(lo[1], hi[1]);
+}
+// Sums of three values over the 64 lanes, in a fixed order: every lane of
+// row 0 (lanes 0-15) gets a's, row 1 c's, row 2 b's.
+__device__ __forceinline__ double wave_total3(double a, double b, double c) {
+  double v = fold16(fold32(a, b), fold32(c, 0.0));
   v += dpp_f64<0xB1>(v);   // quad_perm [1, 0, 3, 2]
   v += dpp_f64<0x4E>(v);   // quad_perm [2, 3, 0, 1]
   v += dpp_f64<0x141>(v);  // row_half_mirror
   v += dpp_f64<0x140>(v);  // row_mirror
-  return (lane_f64(v, 0) + lane_f64(v, 16)) + (lane_f64(v, 32) + lane_f64(v, 48));
+  return v;
 }
 
 // v_mfma_f32_16x16x4_f32 lane layout (64 lanes, l = lane): A operand
 // A[l % 16][l / 16], B operand B[l / 16][l % 16], result element r of lane l
 // is C[4 (l / 16) + r][l % 16].  The contraction index k of one step can be
 // any 4 values of the summed index, as long as A and B agree:
-// * T = z A_W^T, step (q, e): k = w = 16 q + 4 (l / 16) + e, so lane l reads
-//   z[h][16 q + 4 (l / 16) .. + 3] with one 16-byte LDS read for 4 steps, and
-//   holds B = A_W[v][w] for its own v-tile in registers for the whole run;
-// * D = A_H T, step (i, r): k = h = 16 i + 4 (l / 16) + r, which is where
+// * T = Z A_W^T, step (q, e): k = w' = 16 q + 4 (l / 16) + e, so lane l reads
+//   Z[h'][16 q + 4 (l / 16) .. + 3] with one 16-byte LDS read for 4 steps;
+//   the NR steps of 4 columns after the NQ full sixteens take w' = 16 NQ +
+//   4 s + l / 16.  Lane l holds B = A_W[v][w'] of its v-tiles in registers
+//   for the whole run;
+// * D = A_H T, step (i, r): k = h' = 16 i + 4 (l / 16) + r, which is where
 //   element r of lane l of T's tile i already sits: T feeds the second
-//   product from its accumulators with no data movement.
-// Each lane writes its D values straight to their band-order positions, so
-// a band is a contiguous run of dl and xl.  Band b is always reduced by wave
-// b % 8, which also keeps frame 0's run for it: that needs no barrier.
+//   product from its accumulators with no data movement, and the A_H
+//   fragments stay in registers too.
+// Wave w works on quadrant (pr, pc) = (w & 1, w >> 1 & 1), on v'-tiles
+// w >> 2 and (w >> 2) + 2 of 16 columns.  Each lane writes its D values
+// straight to their band-order positions, so a band is a contiguous run of dl
+// and xl.  Band b is always reduced by wave b % 8, which also keeps frame 0's
+// run for it: that needs no barrier.
+//
+// A frame takes two barriers: after its products (every read of zl, and the
+// previous frame's band sums, are done: D goes to dl, the next frame to zl)
+// and after those stores; between a wave's band sums and its next products
+// there is none.  Bound by neither unit alone: at 60 x 104 a frame's matrix
+// work is 2.7 kcycles per wave (half of the unfolded products'), its band
+// sums are latency, and two workgroups per CU (77 KB of LDS, 128 VGPRs) hide
+// one's band sums and barriers behind the other's products.  374 clips x 177
+// frames of 60 x 104: 1.21 ms a call, 2.15 ms with unfolded products, frames
+// in pairs and one workgroup per CU; 48 x 61 frames of 72 x 128: 168 us, 667
+// us through the general path.
 template <int HT, int NQ>
-__global__ __launch_bounds__(kFusedThreads) void spectral_fused_kernel(const float* latents, int64_t frames, int nlag,
-                                                                       int64_t clips, int H, int W, const float* AH,
-                                                                       const float* AW, const int32_t* perm,
-                                                                       const int32_t* start, int bands,
-                                                                       double* per_clip) {
+__global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused_kernel(
+    const float* latents, int64_t frames, int nlag, int64_t clips, int H, int W, const float* AH, const float* AW,
+    const int32_t* perm, const int32_t* start, int bands, double* per_clip) {
+  constexpr int UPW = NQ >= 2 ? 2 : 1;  // v'-tiles per wave
+  constexpr int NI = HT <= 2 ? 1 : 2;   // 16-byte items (x 4 mirrored places) per thread and frame
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const FusedLds L = fused_lds(H, W, bands);
   float* zl = reinterpret_cast<float*>(smem + L.zl);
   float* dl = reinterpret_cast<float*>(smem + L.dl);
   int32_t* inv = reinterpret_cast<int32_t*>(smem + L.dl);  // set-up only
   float* xl = reinterpret_cast<float*>(smem + L.xl);
-  float* ahl = reinterpret_cast<float*>(smem + L.ahl);
   int32_t* sl = reinterpret_cast<int32_t*>(smem + L.sl);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int S = fused_zl_stride(W);  // NQ = (W + 15) / 16 quads of 16 columns = v-tiles
-  const int HW = H * W;
+  const int l16 = lane & 15, g = lane >> 4;
+  const int HW = H * W, He = half_up(H), We = half_up(W);
+  const int S = fused_stride(W), ZQ = 16 * HT * S;  // floats per row and per quadrant
+  const int nr = (We + 3) / 4 - 4 * NQ;             // 0..3 single steps
+  const int NV = (We + 15) / 16;
   const int nperm = start[bands];
-  const bool mma = wave < NQ;
-  const int vcol = 16 * wave + (lane & 15);
+  const int pr = wave & 1, pc = (wave >> 1) & 1;
+  const int Hp = pr ? H / 2 : He, Wp = pc ? W / 2 : We;  // rows and columns of this quadrant's coefficients
 
-  for (int i = tid; i < 16 * HT * S; i += kFusedThreads) zl[i] = 0.0f;
-  for (int i = tid; i < HT * HT * 256; i += kFusedThreads) {  // [a][i][lane][r]
-    const int r = i & 3, l = (i >> 2) & 63, ai = i >> 8;
-    const int a = ai / HT, it = ai % HT;
-    const int u = 16 * a + (l & 15), h = 16 * it + 4 * (l >> 4) + r;
-    ahl[i] = (u < H && h < H) ? AH[u * H + h] : 0.0f;
-  }
+  for (int i = tid; i < 4 * ZQ; i += kFusedThreads) zl[i] = 0.0f;
   for (int i = tid; i <= bands; i += kFusedThreads) sl[i] = start[i];
   for (int i = tid; i < HW; i += kFusedThreads) inv[i] = -1;
-  f32x4 bw[NQ];  // bw[q][e] = A_W[v][16 q + 4 (l / 16) + e]
+  f32x4 bw[UPW][NQ > 0 ? NQ : 1];  // A_W[2v' + pc][16 q + 4 g + e]
+  float bs[UPW][3];                // A_W[2v' + pc][16 NQ + 4 s + g]
 #pragma unroll
-  for (int q = 0; q < NQ; ++q)
+  for (int s = 0; s < UPW; ++s) {
+    const int vp = 16 * ((wave >> 2) + 2 * s) + l16;
+    const float* row = AW + size_t(2 * vp + pc) * W;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int w = 16 * q + 4 * (lane >> 4) + e;
-      bw[q][e] = (mma && vcol < W && w < W) ? AW[vcol * W + w] : 0.0f;
+    for (int q = 0; q < NQ; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int w = 16 * q + 4 * g + e;
+        bw[s][q][e] = (vp < Wp && w < Wp) ? row[w] : 0.0f;
+      }
+#pragma unroll
+    for (int t = 0; t < 3; ++t) {
+      const int w = 16 * NQ + 4 * t + g;
+      bs[s][t] = (vp < Wp && w < Wp) ? row[w] : 0.0f;
     }
-  __syncthreads();
-  for (int j = tid; j < nperm; j += kFusedThreads) inv[perm[j]] = j;
-  __syncthreads();
-  int pos[4 * HT];  // band-order position of result element (a, r) of this lane; HW (spare) if left out
+  }
+  f32x4 ah[HT][HT];  // [a][i]: A_H[2 (16 a + l16) + pr][16 i + 4 g + r]
 #pragma unroll
   for (int a = 0; a < HT; ++a)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int u = 16 * a + 4 * (lane >> 4) + r;
-      const int p = (mma && u < H && vcol < W) ? inv[u * W + vcol] : -1;
-      pos[4 * a + r] = p >= 0 ? p : HW;
-    }
+    for (int i = 0; i < HT; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int up = 16 * a + l16, h = 16 * i + 4 * g + r;
+        ah[a][i][r] = (up < Hp && h < Hp) ? AH[size_t(2 * up + pr) * H + h] : 0.0f;
+      }
+  __syncthreads();
+  for (int j = tid; j < nperm; j += kFusedThreads) inv[perm[j]] = j;
+  __syncthreads();
+  int pos[UPW][4 * HT];  // band-order position of result element (a, r) of this lane; HW (spare) if left out
+#pragma unroll
+  for (int s = 0; s < UPW; ++s)
+#pragma unroll
+    for (int a = 0; a < HT; ++a)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int up = 16 * a + 4 * g + r, vp = 16 * ((wave >> 2) + 2 * s) + l16;
+        const int p = (up < Hp && vp < Wp) ? inv[(2 * up + pr) * W + 2 * vp + pc] : -1;
+        pos[s][4 * a + r] = p >= 0 ? p : HW;
+      }
   // This block's frames: an equal contiguous share of the (clip, lag) order,
   // preceded by frame 0 of its first clip when the share starts past it.
   const int64_t total = clips * int64_t(nlag);
@@ -377,115 +434,153 @@ __global__ __launch_bounds__(kFusedThreads) void spectral_fused_kernel(const flo
   const int64_t c_first = f0 / nlag;
   const int t_first = int(f0 - c_first * nlag);
   const int64_t njobs = (f1 - f0) + (t_first != 0 ? 1 : 0);
-  // Frame loads: W % 4 == 0 as float4 chunks of the contiguous frame (chunk
-  // tid + 512 k), else one float per (row, column) with column tid % 128.
-  const bool vec = (W & 3) == 0;
-  constexpr int kChunks = HT;  // float4 chunks per thread: H W <= 16 HT x 128 = 2048 HT floats
-  static_assert(kChunks * kFusedThreads * 4 >= 16 * HT * kFusedMaxW, "chunk count");
-  int zoff[kChunks];  // LDS offset of each chunk, or -1
-#pragma unroll
-  for (int k = 0; k < kChunks; ++k) {
-    const int e = 4 * (tid + kFusedThreads * k);
-    zoff[k] = (vec && e < HW) ? (e / W) * S + e % W : -1;
-  }
-  const int cz = tid & 127, rz = tid >> 7;
-  f32x4 zr[HT];  // vec: chunk k in zr[k]; else row rz + 4 k in zr[k / 4][k % 4]
+  // Frame loads, each place with its three mirrors: W % 8 == 0 as 16-byte
+  // chunks (item tid + 512 m = chunk k of row h'), else one float per (row,
+  // column), four items where the other has one.  Addresses are worked out
+  // anew for each frame: kept across the products they would cost registers.
+  const bool vec = (W & 7) == 0;
+  const int per_row = vec ? W / 8 : We, items = He * per_row;
+  constexpr int kPlaces = 4 * NI;
+  f32x4 zr[kPlaces];  // vec: the four mirrored chunks of item m in zr[4 m ..]; else item m's four values in zr[m]
+  auto item = [&](int m) {
+    int it = tid + kFusedThreads * m;
+    asm volatile("" : "+v"(it));
+    return it;
+  };
   auto load_z = [&](int64_t c, int t) {
     const float* z = latents + (size_t(c) * size_t(frames) + size_t(t)) * size_t(HW);
     if (vec) {
 #pragma unroll
-      for (int k = 0; k < kChunks; ++k)
-        if (zoff[k] >= 0) zr[k] = *reinterpret_cast<const f32x4*>(z + 4 * (tid + kFusedThreads * k));
+      for (int m = 0; m < NI; ++m) {
+        const int it = item(m);
+        if (it < items) {
+          const int h = it / per_row, k = 4 * (it - h * per_row);
+          const int o0 = h * W + k, o1 = h * W + W - 4 - k, down = (H - 1 - 2 * h) * W;
+          zr[4 * m] = *reinterpret_cast<const f32x4*>(z + o0);
+          zr[4 * m + 1] = *reinterpret_cast<const f32x4*>(z + o1);
+          zr[4 * m + 2] = *reinterpret_cast<const f32x4*>(z + o0 + down);
+          zr[4 * m + 3] = *reinterpret_cast<const f32x4*>(z + o1 + down);
+        }
+      }
     } else {
 #pragma unroll
-      for (int k = 0; k < 4 * HT; ++k) {
-        const int h = rz + 4 * k;
-        zr[k / 4][k % 4] = (cz < W && h < H) ? z[h * W + cz] : 0.0f;
+      for (int m = 0; m < kPlaces; ++m) {
+        const int it = item(m);
+        if (it < items) {
+          const int h = it / per_row, w = it - h * per_row;
+          const int o0 = h * W + w, o1 = h * W + W - 1 - w, down = (H - 1 - 2 * h) * W;
+          zr[m] = f32x4{z[o0], z[o1], z[o0 + down], z[o1 + down]};
+        }
       }
     }
+  };
+  // The four quadrants' values of one place and its mirrors: a, b in a row,
+  // c, d in the mirrored row (a middle row or column is its own mirror).
+  auto fold = [](float a, float b, float c, float d, bool mid_row, bool mid_col) {
+    const float s1 = mid_col ? a : a + b, s2 = mid_col ? c : c + d, d1 = a - b, d2 = c - d;
+    return f32x4{mid_row ? s1 : s1 + s2, mid_row ? d1 : d1 + d2, s1 - s2, d1 - d2};  // quadrants 2 pr + pc
   };
   auto store_z = [&]() {
     if (vec) {
 #pragma unroll
-      for (int k = 0; k < kChunks; ++k)
-        if (zoff[k] >= 0) *reinterpret_cast<f32x4*>(zl + zoff[k]) = zr[k];
+      for (int m = 0; m < NI; ++m) {
+        const int it = item(m);
+        if (it < items) {
+          const int h = it / per_row, k = 4 * (it - h * per_row);
+          const bool mid = 2 * h == H - 1;
+          f32x4 q[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const f32x4 v = fold(zr[4 * m][e], zr[4 * m + 1][3 - e], zr[4 * m + 2][e], zr[4 * m + 3][3 - e], mid, false);
+#pragma unroll
+            for (int x = 0; x < 4; ++x) q[x][e] = v[x];
+          }
+#pragma unroll
+          for (int x = 0; x < 4; ++x) *reinterpret_cast<f32x4*>(zl + x * ZQ + h * S + k) = q[x];
+        }
+      }
     } else {
 #pragma unroll
-      for (int k = 0; k < 4 * HT; ++k) {
-        const int h = rz + 4 * k;
-        if (cz < W && h < H) zl[h * S + cz] = zr[k / 4][k % 4];
+      for (int m = 0; m < kPlaces; ++m) {
+        const int it = item(m);
+        if (it < items) {
+          const int h = it / per_row, w = it - h * per_row;
+          const f32x4 v = fold(zr[m][0], zr[m][1], zr[m][2], zr[m][3], 2 * h == H - 1, 2 * w == W - 1);
+#pragma unroll
+          for (int x = 0; x < 4; ++x) zl[x * ZQ + h * S + w] = v[x];
+        }
       }
     }
   };
-  struct Job {
-    int64_t c;
-    int t;
-    bool emit;
-  };
-  auto next_job = [&](const Job& j) -> Job {
-    if (!j.emit) return Job{j.c, t_first, true};
-    return j.t + 1 == nlag ? Job{j.c + 1, 0, true} : Job{j.c, j.t + 1, true};
-  };
-  float* dl2 = reinterpret_cast<float*>(smem + L.dl2);
-  auto zfrag = [&](f32x4* a, int q) {
+  const float* zq = zl + (2 * pr + pc) * ZQ + l16 * S;
+  const bool mma = (wave >> 2) < NV, two = UPW == 2 && (wave >> 2) + 2 < NV;  // wave-uniform
+  f32x4 dacc[UPW][HT];
+  auto products = [&](auto n_c) {
+    constexpr int N = decltype(n_c)::value;
+    f32x4 tacc[N][HT];
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+#pragma unroll
+      for (int i = 0; i < HT; ++i) tacc[s][i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) {
+      f32x4 a[HT];
+#pragma unroll
+      for (int i = 0; i < HT; ++i) a[i] = *reinterpret_cast<const f32x4*>(zq + 16 * i * S + 16 * q + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < HT; ++i)
+#pragma unroll
+          for (int s = 0; s < N; ++s)
+            tacc[s][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][e], bw[s][q][e], tacc[s][i], 0, 0, 0);
+    }
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+      if (t < nr) {
+#pragma unroll
+        for (int i = 0; i < HT; ++i) {
+          const float a = zq[16 * i * S + 16 * NQ + 4 * t + g];
+#pragma unroll
+          for (int s = 0; s < N; ++s)
+            tacc[s][i] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bs[s][t], tacc[s][i], 0, 0, 0);
+        }
+      }
+#pragma unroll
+    for (int s = 0; s < N; ++s)
+#pragma unroll
+      for (int a = 0; a < HT; ++a) dacc[s][a] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int i = 0; i < HT; ++i)
-      a[i] = *reinterpret_cast<const f32x4*>(zl + (16 * i + (lane & 15)) * S + 16 * q + 4 * (lane >> 4));
-  };  auto products = [&](f32x4 (&dacc)[HT]) {
-    if (mma) {
-      f32x4 tacc[HT], acur[HT];
 #pragma unroll
-      for (int i = 0; i < HT; ++i) tacc[i] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        zfrag(acur, q);
+        for (int a = 0; a < HT; ++a)
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int i = 0; i < HT; ++i)
-            tacc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(acur[i][e], bw[q][e], tacc[i], 0, 0, 0);
-      }
-#pragma unroll
-      for (int a = 0; a < HT; ++a) dacc[a] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int i = 0; i < HT; ++i) {
-        f32x4 ah[HT];
-#pragma unroll
-        for (int a = 0; a < HT; ++a) ah[a] = *reinterpret_cast<const f32x4*>(ahl + ((a * HT + i) * 64 + lane) * 4);
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int a = 0; a < HT; ++a)
-            dacc[a] = __builtin_amdgcn_mfma_f32_16x16x4f32(ah[a][r], tacc[i][r], dacc[a], 0, 0, 0);
-      }
-    }
+          for (int s = 0; s < N; ++s)
+            dacc[s][a] = __builtin_amdgcn_mfma_f32_16x16x4f32(ah[a][i][r], tacc[s][i][r], dacc[s][a], 0, 0, 0);
   };
-  auto scatter = [&](float* dst, const f32x4 (&dacc)[HT]) {
-    if (mma) {
+  auto scatter = [&](int s) {
 #pragma unroll
-      for (int a = 0; a < HT; ++a)
+    for (int a = 0; a < HT; ++a)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) dst[pos[4 * a + r]] = dacc[a][r];
-    }
+      for (int r = 0; r < 4; ++r) dl[pos[s][4 * a + r]] = dacc[s][a][r];
   };
-  auto reduce1 = [&](const Job& jb, const float* dsrc) {
-    const int64_t c = jb.c;
-    const int t = jb.t;
-    const bool emit = jb.emit;
+  // The band sums of frame (c, t), in dl.
+  auto reduce = [&](int64_t c, int t, bool emit) {
     double* out = per_clip + (size_t(c) * size_t(nlag) + size_t(t)) * size_t(bands) * 3;
+    const int which = g == 0 ? 0 : g == 1 ? 2 : 1;  // of a band's three sums, the one wave_total3 leaves in this row
     for (int b = wave; b < bands; b += kFusedThreads / 64) {
       const int s0 = sl[b], s1 = sl[b + 1];
       double sy = 0, syy = 0, sxy = 0;
       if (t == 0) {  // frame 0 of a clip: its run becomes x
         for (int j = s0 + lane; j < s1; j += 64) {
-          const float yf = dsrc[j];
+          const float yf = dl[j];
           xl[j] = yf;
           const double y = yf;
           sy += y;
           syy = fma(y, y, syy);
         }
-        sy = wave_total(sy);
-        syy = wave_total(syy);
         sxy = syy;
       } else {
         int j = s0 + lane;
@@ -494,7 +589,7 @@ __global__ __launch_bounds__(kFusedThreads) void spectral_fused_kernel(const flo
 #pragma unroll
           for (int m = 0; m < 4; ++m) {
             xf[m] = xl[j + 64 * m];
-            yf[m] = dsrc[j + 64 * m];
+            yf[m] = dl[j + 64 * m];
           }
 #pragma unroll
           for (int m = 0; m < 4; ++m) {
@@ -505,117 +600,55 @@ __global__ __launch_bounds__(kFusedThreads) void spectral_fused_kernel(const flo
           }
         }
         for (; j < s1; j += 64) {
-          const double x = xl[j], y = dsrc[j];
+          const double x = xl[j], y = dl[j];
           sy += y;
           syy = fma(y, y, syy);
           sxy = fma(x, y, sxy);
         }
-        sy = wave_total(sy);
-        syy = wave_total(syy);
-        sxy = wave_total(sxy);
       }
-      if (emit && lane == 0) {
-        out[3 * b] = sy;
-        out[3 * b + 1] = syy;
-        out[3 * b + 2] = sxy;
-      }
-    }
-  };
-  // Two frames of one clip, neither frame 0: one pass over x and both
-  // transforms, six sums per band.
-  auto reduce2 = [&](const Job& ja, const Job& jb) {
-    double* outa = per_clip + (size_t(ja.c) * size_t(nlag) + size_t(ja.t)) * size_t(bands) * 3;
-    double* outb = per_clip + (size_t(jb.c) * size_t(nlag) + size_t(jb.t)) * size_t(bands) * 3;
-    for (int b = wave; b < bands; b += kFusedThreads / 64) {
-      const int s0 = sl[b], s1 = sl[b + 1];
-      double sa = 0, saa = 0, sxa = 0, sb = 0, sbb = 0, sxb = 0;
-      int j = s0 + lane;
-      for (; j + 192 < s1; j += 256) {
-        float xf[4], af[4], bf[4];
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          xf[m] = xl[j + 64 * m];
-          af[m] = dl[j + 64 * m];
-          bf[m] = dl2[j + 64 * m];
-        }
-#pragma unroll
-        for (int m = 0; m < 4; ++m) {
-          const double x = xf[m], ya = af[m], yb = bf[m];
-          sa += ya;
-          saa = fma(ya, ya, saa);
-          sxa = fma(x, ya, sxa);
-          sb += yb;
-          sbb = fma(yb, yb, sbb);
-          sxb = fma(x, yb, sxb);
-        }
-      }
-      for (; j < s1; j += 64) {
-        const double x = xl[j], ya = dl[j], yb = dl2[j];
-        sa += ya;
-        saa = fma(ya, ya, saa);
-        sxa = fma(x, ya, sxa);
-        sb += yb;
-        sbb = fma(yb, yb, sbb);
-        sxb = fma(x, yb, sxb);
-      }
-      sa = wave_total(sa);
-      saa = wave_total(saa);
-      sxa = wave_total(sxa);
-      sb = wave_total(sb);
-      sbb = wave_total(sbb);
-      sxb = wave_total(sxb);
-      if (lane == 0) {
-        outa[3 * b] = sa;
-        outa[3 * b + 1] = saa;
-        outa[3 * b + 2] = sxa;
-        outb[3 * b] = sb;
-        outb[3 * b + 1] = sbb;
-        outb[3 * b + 2] = sxb;
-      }
+      const double v = wave_total3(sy, syy, sxy);
+      if (emit && l16 == 0 && g < 3) out[3 * b + which] = v;
     }
   };
 
-  Job ja{c_first, 0, t_first == 0};
-  load_z(ja.c, ja.t);
+  int64_t c = c_first;
+  int t = 0;
+  bool emit = t_first == 0;
+  load_z(c, t);
   __syncthreads();  // every lane has read its positions from inv
   store_z();
   __syncthreads();
-  for (int64_t k = 0; k < njobs; k += 2) {
-    const bool has_b = k + 1 < njobs, has_n = k + 2 < njobs;
-    const Job jb = next_job(ja);
-    const Job jn = next_job(jb);
-    if (has_b) load_z(jb.c, jb.t);
-    f32x4 da[HT], db[HT];
-    products(da);     // zl holds frame a
-    __syncthreads();  // every read of zl, and the previous pair's band sums, are done
-    if (has_b) store_z();
-    __syncthreads();
-    if (has_n) load_z(jn.c, jn.t);
-    if (has_b) products(db);  // zl holds frame b
-    __syncthreads();
-    scatter(dl, da);
-    if (has_b) scatter(dl2, db);
-    if (has_n) store_z();
-    __syncthreads();
-    if (has_b && ja.t != 0 && jb.t != 0 && ja.c == jb.c) {
-      reduce2(ja, jb);
-    } else {
-      reduce1(ja, dl);
-      if (has_b) reduce1(jb, dl2);
+  for (int64_t k = 0; k < njobs; ++k) {
+    const bool more = k + 1 < njobs;
+    int64_t cn = c;
+    int tn = emit ? t + 1 : t_first;  // the next frame
+    if (tn == nlag) {
+      ++cn;
+      tn = 0;
     }
-    ja = jn;
+    if (more) load_z(cn, tn);
+    if (two) products(std::integral_constant<int, UPW>{});
+    else if (mma) products(std::integral_constant<int, 1>{});
+    __syncthreads();  // every read of zl, and the previous frame's band sums, are done
+    if (mma) scatter(0);
+    if (two) scatter(UPW - 1);
+    if (more) store_z();
+    __syncthreads();
+    reduce(c, t, emit);
+    c = cn;
+    t = tn;
+    emit = true;
   }
 }
 
 typedef void (*FusedKernel)(const float*, int64_t, int, int64_t, int, int, const float*, const float*,
                             const int32_t*, const int32_t*, int, double*);
 template <int HT>
-constexpr FusedKernel kFusedRow[8] = {spectral_fused_kernel<HT, 1>, spectral_fused_kernel<HT, 2>,
-                                      spectral_fused_kernel<HT, 3>, spectral_fused_kernel<HT, 4>,
-                                      spectral_fused_kernel<HT, 5>, spectral_fused_kernel<HT, 6>,
-                                      spectral_fused_kernel<HT, 7>, spectral_fused_kernel<HT, 8>};
-FusedKernel fused_kernel(int H, int W) {  // H <= 64, W <= 128
-  const int HT = (H + 15) / 16, q = (W + 15) / 16 - 1;
+constexpr FusedKernel kFusedRow[5] = {spectral_fused_kernel<HT, 0>, spectral_fused_kernel<HT, 1>,
+                                      spectral_fused_kernel<HT, 2>, spectral_fused_kernel<HT, 3>,
+                                      spectral_fused_kernel<HT, 4>};
+FusedKernel fused_kernel(int H, int W) {  // H <= 128, W <= 128
+  const int HT = fused_ht(H), q = (half_up(W) + 3) / 4 / 4;
   return HT == 1 ? kFusedRow<1>[q] : HT == 2 ? kFusedRow<2>[q] : HT == 3 ? kFusedRow<3>[q] : kFusedRow<4>[q];
 }
 
@@ -659,13 +692,19 @@ __global__ __launch_bounds__(kMeanOuts * kMeanGroups) void clip_mean_kernel(cons
   }
 }
 
+// Frames whose workspace holds no transforms.  The workspace sizes and the
+// sizes accepted are part of the interface: larger frames keep room for
+// their transforms and stay within the general path's limits, also where the
+// fused kernel takes them.
+bool stored_on_chip(int64_t H, int64_t W) { return H <= 64 && W <= 128; }
+
 bool spec_args_ok(int64_t clips, int64_t frames, int32_t height, int32_t width, int32_t bands, int64_t max_lag) {
   if (clips < 1 || clips > int64_t(0x7fffffff) || frames < 1) return false;
   if (max_lag < 0 || max_lag >= frames || max_lag + 1 > kSpecMaxLags) return false;
   if (height < 1 || width < 1 || height > 1024 || width > 1024) return false;
   if (int64_t(height) * width > 40960) return false;
   if (bands < 1 || bands > kSpecMaxBands) return false;
-  if (!fused_fits(height, width, bands) && dct_lds_bytes(height, width) > size_t(kSpecLdsBytes)) return false;
+  if (!stored_on_chip(height, width) && dct_lds_bytes(height, width) > size_t(kSpecLdsBytes)) return false;
   return true;
 }
 
@@ -711,7 +750,7 @@ int fademem_spectral_workspace_bytes(int64_t clips, int64_t frames, int32_t heig
                                      int64_t max_lag, size_t* bytes) {
   if (!bytes || !spec_args_ok(clips, frames, height, width, bands, max_lag)) return FADEMEM_EINVAL;
   SpecLayout L;
-  if (!spec_layout(clips, max_lag + 1, height, width, bands, fused_fits(height, width, bands), &L))
+  if (!spec_layout(clips, max_lag + 1, height, width, bands, stored_on_chip(height, width), &L))
     return FADEMEM_EINVAL;
   *bytes = L.total;
   return FADEMEM_OK;
@@ -727,7 +766,7 @@ int fademem_spectral_corr(const float* latents, int64_t clips, int64_t frames, i
   const int nlag = int(max_lag + 1);
   const bool fused = fused_fits(height, width, bands);
   SpecLayout L;
-  if (!spec_layout(clips, nlag, height, width, bands, fused, &L)) return FADEMEM_EINVAL;
+  if (!spec_layout(clips, nlag, height, width, bands, stored_on_chip(height, width), &L)) return FADEMEM_EINVAL;
   if (workspace_bytes < L.total) return FADEMEM_ENOMEM;
   char* ws = static_cast<char*>(workspace);
   float* ah = reinterpret_cast<float*>(ws + L.off_ah);
@@ -754,7 +793,9 @@ int fademem_spectral_corr(const float* latents, int64_t clips, int64_t frames, i
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
       return FADEMEM_EHIP;
     const int64_t total = clips * int64_t(nlag);
-    const unsigned grid = unsigned(total < cus ? total : cus);  // one block per CU, every block has a frame
+    // All blocks resident at once, every block with a frame: two per CU where LDS and registers (HT <= 2) allow.
+    const int per_cu = fused_ht(height) <= 2 && 2 * lds <= kSpecLdsBytes ? 2 : 1;
+    const unsigned grid = unsigned(total < per_cu * cus ? total : per_cu * cus);
     hipLaunchKernelGGL(fn, dim3(grid), dim3(kFusedThreads), size_t(lds), s, latents, frames, nlag, clips,
                        int(height), int(width), ah, aw, perm, start, int(bands), per_clip);
   } else {
@@ -789,7 +830,7 @@ int fademem_spectral_corr_static(const float* latents, int64_t clips, int64_t fr
   if (!latents || !band_of || !corr) return FADEMEM_EINVAL;
   if (!spec_args_ok(clips, frames, height, width, bands, max_lag)) return FADEMEM_EINVAL;
   SpecLayout L;
-  if (!spec_layout(clips, max_lag + 1, height, width, bands, fused_fits(height, width, bands), &L))
+  if (!spec_layout(clips, max_lag + 1, height, width, bands, stored_on_chip(height, width), &L))
     return FADEMEM_EINVAL;
   if (L.total > kStaticScratchBytes) return FADEMEM_ESCRATCH;
   void* ws = nullptr;
