@@ -7,10 +7,10 @@
 //   C_k(lag) = mean_clips Pearson(D(z_0)|B_k, D(z_lag)|B_k).
 //
 // Kernels:
-// * dct_basis_kernel -- A_N[k][n] = s_k cos(pi (2n+1) k / (2N)), s_0 =
-//   sqrt(1/N), s_k = sqrt(2/N), in fp64, stored fp32;
-// * band_order_kernel -- the coefficients grouped by band (a stable
-//   counting sort in one block), so each band is a contiguous index list;
+// * spectral_setup_kernel -- A_N[k][n] = s_k cos(pi (2n+1) k / (2N)), s_0 =
+//   sqrt(1/N), s_k = sqrt(2/N), in fp64, stored fp32, and the coefficients
+//   grouped by band (a stable counting sort), so each band is a contiguous
+//   index list;
 // * spectral_fused_kernel (frames of up to 128 x 128 whose LDS fits) --
 //   persistent blocks, each taking an equal contiguous range of the
 //   (clip, lag) frames: per frame T = z A_W^T and D = A_H T on the fp32
@@ -75,14 +75,6 @@ size_t dct_lds_bytes(int64_t H, int64_t W) {
   return size_t(2 * Hp * Wp + Hp * Hp + Wp * Wp) * 4;
 }
 constexpr int kDctFramesPerBlock = 8;
-
-__global__ void dct_basis_kernel(float* A, int N) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= N * N) return;
-  const int k = i / N, n = i % N;
-  const double s = k == 0 ? sqrt(1.0 / N) : sqrt(2.0 / N);
-  A[i] = float(s * cos(M_PI * (2.0 * n + 1.0) * double(k) / (2.0 * N)));
-}
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
@@ -159,61 +151,100 @@ __global__ __launch_bounds__(kDctThreads) void dct2_kernel(const float* latents,
   }
 }
 
-// Exclusive prefix sum over the block (all threads must call it); *total
-// gets the sum of every thread's value.
-__device__ int block_exclusive_scan(int v, int32_t* wsum, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  int x = v;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int y = __shfl_up(x, o);
-    if (lane >= o) x += y;
+// Set-up of an analysis in one launch, bound by its own chain of latencies
+// (band map load, two passes over it in LDS): 7.9 us at 72 x 128, where two
+// basis kernels and a one-block sort took 34 us:
+// * blocks [0, order_blocks): the coefficients grouped by band, in index
+//   order within a band, those outside [0, bands) left out.  Every block
+//   keeps the band map in LDS; wave w of all takes quarter w % 4 of band w / 4,
+//   counts the coefficients of lower bands and of its own before its quarter
+//   (its first position) and ranks its own 512 at a time, 8 per lane.  inverse: order[i] = the position of coefficient i, H W if
+//   left out (the fused kernel's scatter); else order[position] = i;
+// * the other blocks: A_N[k][n] = s_k cos(pi (2n+1) k / (2N)), s_0 =
+//   sqrt(1/N), s_k = sqrt(2/N), for N = H, then N = W.
+constexpr int kSetupThreads = 512;
+constexpr int kSetupSplit = 4;    // waves per band, each ranking its quarter of the coefficients
+constexpr int kSetupChunk = 512;  // coefficients a wave ranks at a time, 8 per lane
+__host__ __device__ inline int setup_map_len(int HW) { return (HW + kSetupChunk - 1) / kSetupChunk * kSetupChunk; }
+__global__ __launch_bounds__(kSetupThreads) void spectral_setup_kernel(const int32_t* band_of, int H, int W, int bands,
+                                                                       int order_blocks, int inverse, int32_t* order,
+                                                                       int32_t* start, float* AH, float* AW) {
+  extern __shared__ __attribute__((aligned(16))) uint16_t map[];  // [setup_map_len(HW)], 0xffff: left out
+  const int tid = threadIdx.x, HW = H * W;
+  if (int(blockIdx.x) >= order_blocks) {
+    int i = (int(blockIdx.x) - order_blocks) * kSetupThreads + tid;
+    const bool rows = i < H * H;
+    const int N = rows ? H : W;
+    if (!rows) i -= H * H;
+    if (i >= N * N) return;
+    const int k = i / N, n = i % N;
+    const double s = k == 0 ? sqrt(1.0 / N) : sqrt(2.0 / N);
+    (rows ? AH : AW)[i] = float(s * cos(M_PI * (2.0 * n + 1.0) * double(k) / (2.0 * N)));
+    return;
   }
-  __syncthreads();  // wsum is free
-  if (lane == 63) wsum[wave] = x;
+  const int len = setup_map_len(HW);
+  typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+  typedef uint16_t u16x4 __attribute__((ext_vector_type(4)));
+#pragma unroll 5
+  for (int i = 4 * tid; i < len; i += 4 * kSetupThreads) {
+    i32x4 v = {-1, -1, -1, -1};
+    if (i + 3 < HW) {
+      __builtin_memcpy(&v, band_of + i, 16);  // band_of is aligned to 4 bytes only
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        if (i + e < HW) v[e] = band_of[i + e];
+    }
+    u16x4 m;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool in = v[e] >= 0 && v[e] < bands;
+      m[e] = in ? uint16_t(v[e]) : uint16_t(0xffff);
+      if (inverse && blockIdx.x == 0 && i + e < HW && !in) order[i + e] = HW;
+    }
+    *reinterpret_cast<u16x4*>(map + i) = m;
+  }
   __syncthreads();
-  int before = 0, all = 0;
-  for (int w = 0; w < nw; ++w) {
-    const int t = wsum[w];
-    if (w < wave) before += t;
-    all += t;
+  const int w = int(blockIdx.x) * (kSetupThreads / 64) + (tid >> 6), lane = tid & 63;
+  const int b = w / kSetupSplit;
+  if (b >= bands) return;
+  const int part = (len / kSetupChunk + kSetupSplit - 1) / kSetupSplit * kSetupChunk;
+  const int i0 = min(len, (w % kSetupSplit) * part), i1 = min(len, i0 + part);
+  typedef uint16_t u16x8 __attribute__((ext_vector_type(8)));
+  int below = 0;
+#pragma unroll 4
+  for (int i = 8 * lane; i < len; i += kSetupChunk) {
+    const u16x8 m = *reinterpret_cast<const u16x8*>(map + i);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) below += int(m[e]) < b + (i < i0 ? 1 : 0);
   }
-  *total = all;
-  return before + x - v;
-}
-
-// Coefficient indices grouped by band, in index order within a band;
-// entries outside [0, bands) are left out.  One block of 1024 threads with
-// the band map in LDS: thread t counts band t / C in chunk t % C of the map
-// (C = 1024 / bands chunks per band), a block prefix sum gives each (band,
-// chunk) its first position, and the thread writes that chunk's indices of
-// the band in order.
-constexpr int kOrderMaxHW = 40960;
-constexpr int kOrderThreads = 1024;
-__global__ __launch_bounds__(kOrderThreads) void band_order_kernel(const int32_t* band_of, int HW, int bands,
-                                                                   int32_t* perm, int32_t* start) {
-  __shared__ int16_t map[kOrderMaxHW];
-  __shared__ int32_t wsum[kOrderThreads / 64];
-  const int tid = threadIdx.x;
-  for (int i = tid; i < HW; i += kOrderThreads) {
-    const int b = band_of[i];
-    map[i] = int16_t((b >= 0 && b < bands) ? b : -1);
+  for (int o = 32; o > 0; o >>= 1) below += __shfl_xor(below, o);
+  int pos = below;
+  for (int i = i0 + 8 * lane; i < i1; i += kSetupChunk) {
+    const u16x8 m = *reinterpret_cast<const u16x8*>(map + i);
+    int n = 0;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) n += int(m[e]) == b;
+    // Matches of the lanes below (n <= 8: four bits) and of all lanes.
+    int p = pos;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      const uint64_t mask = __ballot((n >> k) & 1);
+      p += __popcll(mask & ((uint64_t(1) << lane) - 1)) << k;
+      pos += __popcll(mask) << k;
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (int(m[e]) == b) {
+        if (inverse) order[i + e] = p;
+        else order[p] = i + e;
+        ++p;
+      }
   }
-  const int C = kOrderThreads / bands;  // bands <= 1024
-  const int b = tid / C, j = tid % C;
-  const bool on = b < bands;
-  const int len = (HW + C - 1) / C;
-  const int i0 = min(HW, j * len), i1 = min(HW, i0 + len);
-  __syncthreads();
-  int n = 0;
-  if (on)
-    for (int i = i0; i < i1; ++i) n += (map[i] == b);
-  int total;
-  int pos = block_exclusive_scan(n, wsum, &total);
-  if (on && j == 0) start[b] = pos;
-  if (tid == 0) start[bands] = total;
-  if (on)
-    for (int i = i0; i < i1; ++i)
-      if (map[i] == b) perm[pos++] = i;
+  if (lane == 0) {
+    if (w % kSetupSplit == 0) start[b] = below;
+    if (w == bands * kSetupSplit - 1) start[bands] = pos;
+  }
 }
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -273,8 +304,7 @@ __host__ __device__ inline int fused_ht(int H) { return (half_up(H) + 15) / 16; 
 
 // Byte offsets of the fused kernel's LDS regions.  zl: the folded frame, four
 // quadrants of 16 HT rows (zero outside H x W); dl: the transform D in band
-// order (at set-up, the inverse of the band order); xl: frame 0's
-// coefficients in band order; sl: the band starts.
+// order; xl: frame 0's coefficients in band order; sl: the band starts.
 struct FusedLds {
   int zl, dl, xl, sl, total;
 };
@@ -361,14 +391,13 @@ __device__ __forceinline__ double wave_total3(double a, double b, double c) {
 template <int HT, int NQ>
 __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused_kernel(
     const float* latents, int64_t frames, int nlag, int64_t clips, int H, int W, const float* AH, const float* AW,
-    const int32_t* perm, const int32_t* start, int bands, double* per_clip) {
+    const int32_t* order, const int32_t* start, int bands, double* per_clip) {
   constexpr int UPW = NQ >= 2 ? 2 : 1;  // v'-tiles per wave
   constexpr int NI = HT <= 2 ? 1 : 2;   // 16-byte items (x 4 mirrored places) per thread and frame
   extern __shared__ __attribute__((aligned(16))) char smem[];
   const FusedLds L = fused_lds(H, W, bands);
   float* zl = reinterpret_cast<float*>(smem + L.zl);
   float* dl = reinterpret_cast<float*>(smem + L.dl);
-  int32_t* inv = reinterpret_cast<int32_t*>(smem + L.dl);  // set-up only
   float* xl = reinterpret_cast<float*>(smem + L.xl);
   int32_t* sl = reinterpret_cast<int32_t*>(smem + L.sl);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -377,13 +406,11 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
   const int S = fused_stride(W), ZQ = 16 * HT * S;  // floats per row and per quadrant
   const int nr = (We + 3) / 4 - 4 * NQ;             // 0..3 single steps
   const int NV = (We + 15) / 16;
-  const int nperm = start[bands];
   const int pr = wave & 1, pc = (wave >> 1) & 1;
   const int Hp = pr ? H / 2 : He, Wp = pc ? W / 2 : We;  // rows and columns of this quadrant's coefficients
 
   for (int i = tid; i < 4 * ZQ; i += kFusedThreads) zl[i] = 0.0f;
   for (int i = tid; i <= bands; i += kFusedThreads) sl[i] = start[i];
-  for (int i = tid; i < HW; i += kFusedThreads) inv[i] = -1;
   f32x4 bw[UPW][NQ > 0 ? NQ : 1];  // A_W[2v' + pc][16 q + 4 g + e]
   float bs[UPW][3];                // A_W[2v' + pc][16 NQ + 4 s + g]
 #pragma unroll
@@ -413,9 +440,6 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
         const int up = 16 * a + l16, h = 16 * i + 4 * g + r;
         ah[a][i][r] = (up < Hp && h < Hp) ? AH[size_t(2 * up + pr) * H + h] : 0.0f;
       }
-  __syncthreads();
-  for (int j = tid; j < nperm; j += kFusedThreads) inv[perm[j]] = j;
-  __syncthreads();
   int pos[UPW][4 * HT];  // band-order position of result element (a, r) of this lane; HW (spare) if left out
 #pragma unroll
   for (int s = 0; s < UPW; ++s)
@@ -424,8 +448,7 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int up = 16 * a + 4 * g + r, vp = 16 * ((wave >> 2) + 2 * s) + l16;
-        const int p = (up < Hp && vp < Wp) ? inv[(2 * up + pr) * W + 2 * vp + pc] : -1;
-        pos[s][4 * a + r] = p >= 0 ? p : HW;
+        pos[s][4 * a + r] = (up < Hp && vp < Wp) ? order[(2 * up + pr) * W + 2 * vp + pc] : HW;
       }
   // This block's frames: an equal contiguous share of the (clip, lag) order,
   // preceded by frame 0 of its first clip when the share starts past it.
@@ -615,7 +638,7 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
   int t = 0;
   bool emit = t_first == 0;
   load_z(c, t);
-  __syncthreads();  // every lane has read its positions from inv
+  __syncthreads();  // zl is cleared
   store_z();
   __syncthreads();
   for (int64_t k = 0; k < njobs; ++k) {
@@ -657,11 +680,12 @@ FusedKernel fused_kernel(int H, int W) {  // H <= 128, W <= 128
 // S_x, S_xx):
 //   r = (n S_xy - S_x S_y) / sqrt((n S_xx - S_x^2)(n S_yy - S_y^2)),
 // NaN for a band without spread; then the mean over clips into
-// corr[band][lag].  Block = 16 consecutive (lag, band) outputs x 16 clip
-// groups: group g takes clips g, g + 16, ... in order, then the 16 partial
+// corr[band][lag].  Block = 8 consecutive (lag, band) outputs x 32 clip
+// groups: group g takes clips g, g + 32, ... in order, then the 32 partial
 // sums are added in group order (a fixed order, so every call gives the
-// same bits).
-constexpr int kMeanOuts = 16, kMeanGroups = 16;
+// same bits).  Bound by the latency of the sums' loads: four clips' loads in
+// flight per thread.
+constexpr int kMeanOuts = 8, kMeanGroups = 32;
 __global__ __launch_bounds__(kMeanOuts * kMeanGroups) void clip_mean_kernel(const double* per_clip,
                                                                            const int32_t* start, int64_t clips,
                                                                            int nlag, int bands, double* corr) {
@@ -673,6 +697,7 @@ __global__ __launch_bounds__(kMeanOuts * kMeanGroups) void clip_mean_kernel(cons
   if (i < n_out) {
     const int b = int(i % bands);
     const double n = double(start[b + 1] - start[b]);
+#pragma unroll 4
     for (int64_t c = g; c < clips; c += kMeanGroups) {
       const double* f = per_clip + (size_t(c) * size_t(n_out) + size_t(i)) * 3;
       const double* f0 = per_clip + (size_t(c) * size_t(n_out) + size_t(b)) * 3;  // lag 0
@@ -778,9 +803,15 @@ int fademem_spectral_corr(const float* latents, int64_t clips, int64_t frames, i
   hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const int HW = height * width;
   (void)hipGetLastError();
-  hipLaunchKernelGGL(dct_basis_kernel, dim3((height * height + 255) / 256), dim3(256), 0, s, ah, int(height));
-  hipLaunchKernelGGL(dct_basis_kernel, dim3((width * width + 255) / 256), dim3(256), 0, s, aw, int(width));
-  hipLaunchKernelGGL(band_order_kernel, dim3(1), dim3(kOrderThreads), 0, s, band_of, HW, int(bands), perm, start);
+  const int order_blocks = (int(bands) * kSetupSplit * 64 + kSetupThreads - 1) / kSetupThreads;
+  const int basis_blocks = (height * height + width * width + kSetupThreads - 1) / kSetupThreads;
+  const size_t map_bytes = size_t(setup_map_len(HW)) * sizeof(uint16_t);
+  if (map_bytes > 64 * 1024 &&
+      hipFuncSetAttribute(reinterpret_cast<const void*>(spectral_setup_kernel),
+                          hipFuncAttributeMaxDynamicSharedMemorySize, int(map_bytes)) != hipSuccess)
+    return FADEMEM_EHIP;
+  hipLaunchKernelGGL(spectral_setup_kernel, dim3(unsigned(order_blocks + basis_blocks)), dim3(kSetupThreads), map_bytes,
+                     s, band_of, int(height), int(width), int(bands), order_blocks, fused ? 1 : 0, perm, start, ah, aw);
   if (fused) {
     const int lds = fused_lds(height, width, bands).total;
     const FusedKernel fn = fused_kernel(height, width);
