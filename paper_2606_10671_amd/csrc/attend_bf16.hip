@@ -107,7 +107,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleBound = 256.0f;  // redo a tile whose weights exceed 2^8
 constexpr int kSegOverhead = 2;          // key tiles' worth of time a segment's prologue and epilogue cost
-constexpr int kMinSplit = 10;            // key tiles a query tile needs to be split at all
+constexpr int kMinSplit = 6;             // key tiles a query tile needs to be split at all
 constexpr int kMinPart = 6;              // key tiles of a head part at least
 constexpr int kMinTailSaves = 2;         // key tiles a tail has to take off each head part
 constexpr int kMaxParts = 64;            // head parts of a query tile at most

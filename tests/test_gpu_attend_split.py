@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,D,q_tokens,keys", [
-    (2, 128, 40, 9 * 64),          # below the smallest split: one workgroup per tile
-    (2, 128, 40, 9 * 64 + 1),      # 10 key tiles: one head part and a tail
+    (2, 128, 40, 5 * 64),          # below the smallest split: one workgroup per tile
+    (2, 128, 40, 5 * 64 + 1),      # 6 key tiles: one head part and a tail
     (1, 64, 256, 12 * 64),         # two head parts and a tail
     (3, 128, 33, 63 * 64 + 5),     # 10 head parts, the second wave with one query
     (3, 64, 300, 64 * 64),         # a second query tile of 44 queries
