@@ -37,11 +37,11 @@ __host__ __device__ constexpr size_t attend_ws_bytes(int head_dim) {
   return 2 * size_t(kSkMaxGroups) * attend_slot_floats(head_dim) * sizeof(float);
 }
 
-// fp32 attention work split: a workgroup takes kF32Queries queries of one
-// head over a range of key tiles; when the key axis is cut into several
-// ranges, each leaves its partial result (unnormalised O, row max and row
-// sum per query) in a slot and a second kernel combines them.  At most
-// kF32MaxParts slots per call.
+// fp32 attention work split: a workgroup takes 64 or 128 queries of one head
+// over a range of key tiles; when the key axis is cut into several ranges,
+// each leaves its partial result (unnormalised O, row max and row sum per
+// query) in a slot and a second kernel combines them.  The scratch holds
+// kF32MaxParts slots of kF32Queries queries, or half as many of twice that.
 constexpr int kF32Queries = 64;
 constexpr int kF32MaxParts = 512;
 __host__ __device__ constexpr size_t f32_part_floats(int head_dim) {
@@ -131,7 +131,7 @@ struct AttendArgs {
   int64_t tokens_per_block;   // N
   int64_t cur_tokens;         // rows of the current chunk
   int64_t q_tokens;
-  float* ws;                  // attention scratch: 2*kSkMaxGroups slots (bf16), kF32MaxParts slots (fp32)
+  float* ws;                  // attention scratch: 2*kSkMaxGroups slots (bf16), f32_ws_bytes (fp32)
   int heads;
   int head_dim;
   float scale;
