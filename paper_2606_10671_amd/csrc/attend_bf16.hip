@@ -888,15 +888,14 @@ hipError_t launch_d(AttnKernel kernel, AttnKernel merge2, AttnKernel merge_n, st
                             32 * 1024);
   });
   if (e != hipSuccess) return e;
-  int dev = 0, cus = 0, per_cu = 0;
+  // One workgroup per CU: its tile buffers (96 KB of 160 at D = 128) and
+  // registers (186 of 512 per SIMD lane, two waves each, at D = 64) leave no
+  // room for a second.
+  int dev = 0, cus = 0;
   if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
   if ((e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess) return e;
-  if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kernel), kThreads,
-                                                        shmem)) != hipSuccess)
-    return e;
-  long long groups = (long long)(cus > 0 ? cus : 1) * (per_cu > 0 ? per_cu : 1);
-  if (groups > kSkMaxGroups) groups = kSkMaxGroups;
-  plan.groups = int(groups);
+  const int groups = std::max(1, std::min(cus, kSkMaxGroups));
+  plan.groups = groups;
   plan.rounds = total / plan.groups;
   plan.rem = total - plan.rounds * plan.groups;
   plan.heads_per = 1;

@@ -8,6 +8,7 @@ library is not built, loading fails loudly -- there is no fallback.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional, Sequence
 
@@ -139,6 +140,12 @@ def _ok(rc: int, where: str) -> None:
         raise FademError(rc, where)
 
 
+@functools.lru_cache(maxsize=64)
+def _pointers(n: int):
+    """The ctypes array type of n device pointers (building the type costs more than filling one)."""
+    return ctypes.c_void_p * n
+
+
 def make_config(budget: int, heads: int, head_dim: int, tokens_per_block: int, beta: float = 0.3,
                 anchor: bool = True, dtype: int = FADEMEM_BF16, layers: int = 1,
                 merge_op: int = FADEMEM_MERGE_SQRT_SPAN, rope_pairs: int = 0,
@@ -167,33 +174,29 @@ def fademem_cache_destroy(handle: int) -> None:
     _ok(lib().fademem_cache_destroy(ctypes.c_void_p(handle)), "fademem_cache_destroy")
 
 
+# The argument types declared in lib() convert plain integers (0 is NULL) and
+# floats, so the calls of a chunk step pass them as they are.
+
 def fademem_insert(handle: int, k_ptrs: Sequence[int], v_ptrs: Sequence[int], position: int,
                    stream: int = 0) -> None:
-    n = len(k_ptrs)
-    ka = (ctypes.c_void_p * n)(*k_ptrs)
-    va = (ctypes.c_void_p * n)(*v_ptrs)
-    _ok(lib().fademem_insert(ctypes.c_void_p(handle), ka, va, position, ctypes.c_void_p(stream)), "fademem_insert")
+    arr = _pointers(len(k_ptrs))
+    _ok(lib().fademem_insert(handle, arr(*k_ptrs), arr(*v_ptrs), position, stream), "fademem_insert")
 
 
 def fademem_consolidate(handle: int, stream: int = 0) -> None:
-    _ok(lib().fademem_consolidate(ctypes.c_void_p(handle), ctypes.c_void_p(stream)), "fademem_consolidate")
+    _ok(lib().fademem_consolidate(handle, stream), "fademem_consolidate")
 
 
 def fademem_update(handle: int, k_ptrs: Sequence[int], v_ptrs: Sequence[int], frames: int, first_position: int,
                    stream: int = 0) -> None:
-    n = len(k_ptrs)
-    ka = (ctypes.c_void_p * n)(*k_ptrs)
-    va = (ctypes.c_void_p * n)(*v_ptrs)
-    _ok(lib().fademem_update(ctypes.c_void_p(handle), ka, va, frames, first_position, ctypes.c_void_p(stream)),
-        "fademem_update")
+    arr = _pointers(len(k_ptrs))
+    _ok(lib().fademem_update(handle, arr(*k_ptrs), arr(*v_ptrs), frames, first_position, stream), "fademem_update")
 
 
 def fademem_attend(handle: int, layer: int, q_ptr: int, q_tokens: int, k_cur_ptr: int, v_cur_ptr: int,
                    cur_tokens: int, scale: float, out_ptr: int, lse_ptr: int = 0, stream: int = 0) -> None:
-    _ok(lib().fademem_attend(ctypes.c_void_p(handle), layer, ctypes.c_void_p(q_ptr), q_tokens,
-                             ctypes.c_void_p(k_cur_ptr), ctypes.c_void_p(v_cur_ptr), cur_tokens,
-                             ctypes.c_float(scale), ctypes.c_void_p(out_ptr), ctypes.c_void_p(lse_ptr),
-                             ctypes.c_void_p(stream)), "fademem_attend")
+    _ok(lib().fademem_attend(handle, layer, q_ptr, q_tokens, k_cur_ptr, v_cur_ptr, cur_tokens, scale, out_ptr,
+                             lse_ptr, stream), "fademem_attend")
 
 
 def fademem_stage(handle: int, layers: int, frames: int):
@@ -205,15 +208,13 @@ def fademem_stage(handle: int, layers: int, frames: int):
 
 
 def fademem_update_staged(handle: int, frames: int, first_position: int, stream: int = 0) -> None:
-    _ok(lib().fademem_update_staged(ctypes.c_void_p(handle), frames, first_position, ctypes.c_void_p(stream)),
-        "fademem_update_staged")
+    _ok(lib().fademem_update_staged(handle, frames, first_position, stream), "fademem_update_staged")
 
 
 def fademem_attend_staged(handle: int, layer: int, q_ptr: int, q_tokens: int, frames: int, scale: float,
                           out_ptr: int, lse_ptr: int = 0, stream: int = 0) -> None:
-    _ok(lib().fademem_attend_staged(ctypes.c_void_p(handle), layer, ctypes.c_void_p(q_ptr), q_tokens, frames,
-                                    ctypes.c_float(scale), ctypes.c_void_p(out_ptr), ctypes.c_void_p(lse_ptr),
-                                    ctypes.c_void_p(stream)), "fademem_attend_staged")
+    _ok(lib().fademem_attend_staged(handle, layer, q_ptr, q_tokens, frames, scale, out_ptr, lse_ptr, stream),
+        "fademem_attend_staged")
 
 
 def fademem_verify(handle: int, stream: int = 0) -> None:
@@ -281,10 +282,8 @@ def fademem_spectral_workspace_bytes(clips: int, frames: int, height: int, width
 def fademem_spectral_corr(latents_ptr: int, clips: int, frames: int, height: int, width: int, band_of_ptr: int,
                           bands: int, max_lag: int, workspace_ptr: int, workspace_bytes: int, corr_ptr: int,
                           stream: int = 0) -> None:
-    _ok(lib().fademem_spectral_corr(ctypes.c_void_p(latents_ptr), clips, frames, height, width,
-                                    ctypes.c_void_p(band_of_ptr), bands, max_lag, ctypes.c_void_p(workspace_ptr),
-                                    workspace_bytes, ctypes.c_void_p(corr_ptr), ctypes.c_void_p(stream)),
-        "fademem_spectral_corr")
+    _ok(lib().fademem_spectral_corr(latents_ptr, clips, frames, height, width, band_of_ptr, bands, max_lag,
+                                    workspace_ptr, workspace_bytes, corr_ptr, stream), "fademem_spectral_corr")
 
 
 def fademem_spectral_corr_static(latents_ptr: int, clips: int, frames: int, height: int, width: int,
@@ -322,6 +321,17 @@ def fademem_strerror(code: int) -> str:
 
 # -- torch-facing owner ----------------------------------------------------------
 
+def current_stream() -> int:
+    """The hipStream_t of torch's current stream on the current device.  Read
+    as a plain integer where this torch offers that (a Stream object per call
+    costs 1-2 us, more than a small kernel's launch)."""
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return int(torch.cuda.current_stream().cuda_stream)
+    return int(raw(torch.cuda.current_device()))
+
+
 class Cache:
     """Owns a device pool (a torch uint8 tensor) and a library handle.
 
@@ -344,6 +354,7 @@ class Cache:
                                FADEMEM_BF16 if dtype == torch.bfloat16 else FADEMEM_F32, layers,
                                merge_op=MERGE_OPS[merge_op], rope_pairs=rope_pairs, rope_theta=rope_theta,
                                stage_frames=stage_frames)
+        self._tail = (int(heads), int(head_dim))  # a tensor's shape after its tokens
         self.device = torch.device("cuda") if device is None else torch.device(device)
         self.pool_bytes = fademem_pool_bytes(self.cfg)
         self.pool = torch.empty(self.pool_bytes, dtype=torch.uint8, device=self.device)
@@ -351,16 +362,17 @@ class Cache:
 
     @staticmethod
     def _stream(stream) -> int:
-        import torch
-        s = torch.cuda.current_stream() if stream is None else stream
-        return int(s.cuda_stream)
+        if stream is None:
+            return current_stream()
+        return int(stream.cuda_stream)
 
     def _check(self, t, rows: Optional[int] = None, name: str = "tensor"):
-        if t.dtype != self.torch_dtype or not t.is_contiguous() or t.device.type != "cuda":
+        if t.dtype != self.torch_dtype or not t.is_contiguous() or not t.is_cuda:
             raise ValueError(f"{name}: expected a contiguous {self.torch_dtype} CUDA tensor")
-        if t.dim() != 3 or t.shape[1] != self.cfg.heads or t.shape[2] != self.cfg.head_dim:
+        shape = t.shape
+        if len(shape) != 3 or shape[1:] != self._tail:
             raise ValueError(f"{name}: expected [tokens][{self.cfg.heads}][{self.cfg.head_dim}]")
-        if rows is not None and t.shape[0] != rows:
+        if rows is not None and shape[0] != rows:
             raise ValueError(f"{name}: expected {rows} tokens")
 
     def insert(self, k, v, position: int, stream=None):

@@ -41,9 +41,9 @@ def spectral_corr(latents, band_of, bands: int, max_lag: int, stream=None):
     need = fm.fademem_spectral_workspace_bytes(clips, frames, H, W, bands, max_lag)
     ws = torch.empty(need, dtype=torch.uint8, device=latents.device)
     corr = torch.empty((bands, max_lag + 1), dtype=torch.float64, device=latents.device)
-    s = torch.cuda.current_stream() if stream is None else stream
+    s = fm.current_stream() if stream is None else int(stream.cuda_stream)
     fm.fademem_spectral_corr(latents.data_ptr(), clips, frames, H, W, band_of.data_ptr(), bands, max_lag,
-                             ws.data_ptr(), need, corr.data_ptr(), int(s.cuda_stream))
+                             ws.data_ptr(), need, corr.data_ptr(), s)
     return corr
 
 
