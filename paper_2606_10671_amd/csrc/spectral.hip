@@ -381,13 +381,14 @@ __device__ __forceinline__ double wave_total3(double a, double b, double c) {
 // A frame takes two barriers: after its products (every read of zl, and the
 // previous frame's band sums, are done: D goes to dl, the next frame to zl)
 // and after those stores; between a wave's band sums and its next products
-// there is none.  Bound by neither unit alone: at 60 x 104 a frame's matrix
-// work is 2.7 kcycles per wave (half of the unfolded products'), its band
-// sums are latency, and two workgroups per CU (77 KB of LDS, 128 VGPRs) hide
-// one's band sums and barriers behind the other's products.  374 clips x 177
-// frames of 60 x 104: 1.21 ms a call, 2.15 ms with unfolded products, frames
-// in pairs and one workgroup per CU; 48 x 61 frames of 72 x 128: 168 us, 667
-// us through the general path.
+// there is none.  Bound by the matrix cores and the vector ALUs together: fp32
+// matrix instructions do not run beside vector ones on a SIMD (their
+// co-execution counter reads 0), so a frame costs the products (840 us of a
+// call on 374 clips x 177 frames of 60 x 104, the band sums, folds and stores
+// left out) plus the rest (560 us alone), less what two workgroups per CU (77
+// KB of LDS, 128 VGPRs) hide of the waits.  That call: 1.15 ms, 2.15 ms with
+// unfolded products, frames in pairs and one workgroup per CU; 48 x 61 frames
+// of 72 x 128: 131 us, 667 us through the general path.
 template <int HT, int NQ>
 __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused_kernel(
     const float* latents, int64_t frames, int nlag, int64_t clips, int H, int W, const float* AH, const float* AW,
@@ -463,6 +464,9 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
   // anew for each frame: kept across the products they would cost registers.
   const bool vec = (W & 7) == 0;
   const int per_row = vec ? W / 8 : We, items = He * per_row;
+  // it / per_row for it < 2^16: a multiplication by 2^32 / per_row, rounded up.
+  const unsigned magic = per_row > 1 ? unsigned(((1ull << 32) + per_row - 1) / per_row) : 0u;
+  auto row_of = [&](int it) { return per_row > 1 ? int(__umulhi(unsigned(it), magic)) : it; };
   constexpr int kPlaces = 4 * NI;
   f32x4 zr[kPlaces];  // vec: the four mirrored chunks of item m in zr[4 m ..]; else item m's four values in zr[m]
   auto item = [&](int m) {
@@ -477,7 +481,7 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
       for (int m = 0; m < NI; ++m) {
         const int it = item(m);
         if (it < items) {
-          const int h = it / per_row, k = 4 * (it - h * per_row);
+          const int h = row_of(it), k = 4 * (it - h * per_row);
           const int o0 = h * W + k, o1 = h * W + W - 4 - k, down = (H - 1 - 2 * h) * W;
           zr[4 * m] = *reinterpret_cast<const f32x4*>(z + o0);
           zr[4 * m + 1] = *reinterpret_cast<const f32x4*>(z + o1);
@@ -490,7 +494,7 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
       for (int m = 0; m < kPlaces; ++m) {
         const int it = item(m);
         if (it < items) {
-          const int h = it / per_row, w = it - h * per_row;
+          const int h = row_of(it), w = it - h * per_row;
           const int o0 = h * W + w, o1 = h * W + W - 1 - w, down = (H - 1 - 2 * h) * W;
           zr[m] = f32x4{z[o0], z[o1], z[o0 + down], z[o1 + down]};
         }
@@ -498,10 +502,11 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
     }
   };
   // The four quadrants' values of one place and its mirrors: a, b in a row,
-  // c, d in the mirrored row (a middle row or column is its own mirror).
-  auto fold = [](float a, float b, float c, float d, bool mid_row, bool mid_col) {
-    const float s1 = mid_col ? a : a + b, s2 = mid_col ? c : c + d, d1 = a - b, d2 = c - d;
-    return f32x4{mid_row ? s1 : s1 + s2, mid_row ? d1 : d1 + d2, s1 - s2, d1 - d2};  // quadrants 2 pr + pc
+  // c, d in the mirrored row.  In a middle row (column) the mirror is the
+  // place itself: fr (fc) is 0 there, else 1.
+  auto fold = [](float a, float b, float c, float d, float fr, float fc) {
+    const float s1 = __builtin_fmaf(b, fc, a), s2 = __builtin_fmaf(d, fc, c), d1 = a - b, d2 = c - d;
+    return f32x4{__builtin_fmaf(s2, fr, s1), __builtin_fmaf(d2, fr, d1), s1 - s2, d1 - d2};  // quadrants 2 pr + pc
   };
   auto store_z = [&]() {
     if (vec) {
@@ -509,12 +514,12 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
       for (int m = 0; m < NI; ++m) {
         const int it = item(m);
         if (it < items) {
-          const int h = it / per_row, k = 4 * (it - h * per_row);
-          const bool mid = 2 * h == H - 1;
+          const int h = row_of(it), k = 4 * (it - h * per_row);
+          const float fr = 2 * h == H - 1 ? 0.0f : 1.0f;
           f32x4 q[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const f32x4 v = fold(zr[4 * m][e], zr[4 * m + 1][3 - e], zr[4 * m + 2][e], zr[4 * m + 3][3 - e], mid, false);
+            const f32x4 v = fold(zr[4 * m][e], zr[4 * m + 1][3 - e], zr[4 * m + 2][e], zr[4 * m + 3][3 - e], fr, 1.0f);
 #pragma unroll
             for (int x = 0; x < 4; ++x) q[x][e] = v[x];
           }
@@ -527,8 +532,9 @@ __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused
       for (int m = 0; m < kPlaces; ++m) {
         const int it = item(m);
         if (it < items) {
-          const int h = it / per_row, w = it - h * per_row;
-          const f32x4 v = fold(zr[m][0], zr[m][1], zr[m][2], zr[m][3], 2 * h == H - 1, 2 * w == W - 1);
+          const int h = row_of(it), w = it - h * per_row;
+          const f32x4 v = fold(zr[m][0], zr[m][1], zr[m][2], zr[m][3], 2 * h == H - 1 ? 0.0f : 1.0f,
+                               2 * w == W - 1 ? 0.0f : 1.0f);
 #pragma unroll
           for (int x = 0; x < 4; ++x) zl[x * ZQ + h * S + w] = v[x];
         }
