@@ -30,9 +30,11 @@
 //   the range's partial result to its slot, and attend_f32_combine_kernel
 //   combines a query tile's ranges in order.
 // Bound by the matrix cores (a tile of 32 keys x 32 queries is 2 x 64 MFMAs
-// of 64 cycles at D = 128): 12 heads x 1170 queries over 5850 keys take 438 us
-// (96 TFLOP/s of the 157 peak; 1137 us on the vector ALUs with K/V broadcast
-// from LDS), and the error against 64 bits falls from 3.1e-7 to 1.6e-7.
+// of 64 cycles at D = 128) and, since fp32 matrix instructions do not run
+// beside vector ones on a SIMD, by the vector work of the softmax and the
+// loads' addresses: 12 heads x 1170 queries over 5850 keys take 418 us (100
+// TFLOP/s of the 157 peak; 1137 us on the vector ALUs with K/V broadcast from
+// LDS), and the error against 64 bits falls from 3.1e-7 to 1.6e-7.
 #include <algorithm>
 #include <mutex>
 
@@ -89,7 +91,9 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
   __shared__ __attribute__((aligned(16))) float v_lds0[S::OBJ];
   __shared__ __attribute__((aligned(16))) float k_lds1[S::NBUF == 2 ? S::OBJ : 4];
   __shared__ __attribute__((aligned(16))) float v_lds1[S::NBUF == 2 ? S::OBJ : 4];
-  extern __shared__ int32_t order_s[];  // K block index of entry e at 2e, V block index at 2e + 1
+  // K and V addresses of row 0 (this head) of each exposed entry, the current
+  // chunk as entry n_entries.
+  extern __shared__ __attribute__((aligned(16))) const char* rows_s[];
 
   const int part = blockIdx.x % parts;
   const int h = (blockIdx.x / parts) / q_tiles;
@@ -109,9 +113,15 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
   const size_t row_bytes = size_t(H) * D * 4;
   const size_t head_off = size_t(h) * D * 4;
 
-  for (int e = tid; e < n_entries; e += kThreads) {
-    order_s[2 * e] = args.k_order ? args.k_order[e] : e;
-    order_s[2 * e + 1] = args.v_order[e];
+  for (int e = tid; e <= n_entries; e += kThreads) {
+    const char* kr = static_cast<const char*>(args.k_cur);
+    const char* vr = static_cast<const char*>(args.v_cur);
+    if (e < n_entries) {
+      kr = args.k_base + size_t(args.k_order ? args.k_order[e] : e) * args.k_stride;
+      vr = args.v_base + size_t(args.v_order[e]) * args.v_stride;
+    }
+    rows_s[2 * e] = kr + head_off;
+    rows_s[2 * e + 1] = vr + head_off;
   }
 
   // Query l32, elements 8 j + 4 hh + e, in the log2 domain.
@@ -143,28 +153,34 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
     vb += split * S::TILE;
     int ln = lane;  // kept from one tile to the next, the addresses would cost registers
     asm volatile("" : "+v"(ln));
+    // The tile's first row: entry e0, row r0 of it (a division per tile; a
+    // row of its own only where entries are shorter than a tile).
+    const int k0 = tile * kTile;
+    const bool in_mem = k0 < mem_rows;
+    const int e0 = in_mem ? k0 / N : n_entries, r0 = in_mem ? k0 - e0 * N : k0 - mem_rows;
 #pragma unroll
     for (int i = 0; i < S::LOADS; ++i) {
       const int idx = (i * QW + qw) * 64 + ln;  // destination chunk
       const int row = idx / S::CH, pos = idx % S::CH;
-      const int k = tile * kTile + row;
-      if (k < Lk) {
-        const char *kr, *vr;
-        size_t off;
-        if (k < mem_rows) {
-          const int e = k / N;
-          kr = args.k_base + size_t(order_s[2 * e]) * args.k_stride;
-          vr = args.v_base + size_t(order_s[2 * e + 1]) * args.v_stride;
-          off = size_t(k - e * N);
+      if (k0 + row < Lk) {
+        int e = e0, r = r0 + row;
+        if (N >= kTile) {
+          if (in_mem && r >= N) {
+            r -= N;
+            ++e;
+          }
+        } else if (k0 + row < mem_rows) {
+          e = (k0 + row) / N;
+          r = k0 + row - e * N;
         } else {
-          kr = static_cast<const char*>(args.k_cur);
-          vr = static_cast<const char*>(args.v_cur);
-          off = size_t(k - mem_rows);
+          e = n_entries;
+          r = k0 + row - mem_rows;
         }
-        off = off * row_bytes + head_off;
-        __builtin_amdgcn_global_load_lds(kr + off + (pos ^ (row & 15)) * 16, (LDS_AS void*)(kb + (i * QW + qw) * 256),
-                                         16, 0, 0);
-        __builtin_amdgcn_global_load_lds(vr + off + pos * 16, (LDS_AS void*)(vb + (i * QW + qw) * 256), 16, 0, 0);
+        const size_t off = size_t(r) * row_bytes;
+        __builtin_amdgcn_global_load_lds(rows_s[2 * e] + off + (pos ^ (row & 15)) * 16,
+                                         (LDS_AS void*)(kb + (i * QW + qw) * 256), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds(rows_s[2 * e + 1] + off + pos * 16,
+                                         (LDS_AS void*)(vb + (i * QW + qw) * 256), 16, 0, 0);
       } else {
         *reinterpret_cast<f32x4*>(kb + idx * 4) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
         *reinterpret_cast<f32x4*>(vb + idx * 4) = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -178,16 +194,17 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
     int swz = (l32 & 15) ^ hh;  // worked out anew for each tile, as in issue()
     asm volatile("" : "+v"(swz));
     const float* vr = vb + split * S::TILE;
-    f32x16 s, s1;  // two chains of D / 4 steps
+    f32x16 zero;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) s[r] = s1[r] = 0.0f;
+    for (int r = 0; r < 16; ++r) zero[r] = 0.0f;
+    f32x16 s, s1;  // two chains of D / 4 steps
 #pragma unroll
     for (int j = 0; j < D / 8; ++j) {
       const f32x4 kf = *reinterpret_cast<const f32x4*>(kr + ((2 * j) ^ swz) * 4);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        if (e % 2 == 0) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q[j][e], s, 0, 0, 0);
-        else s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q[j][e], s1, 0, 0, 0);
+        if (e % 2 == 0) s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q[j][e], j + e == 0 ? zero : s, 0, 0, 0);
+        else s1 = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[e], q[j][e], j + e == 1 ? zero : s1, 0, 0, 0);
       }
     }
 #pragma unroll
@@ -202,12 +219,12 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     const float m_new = fmaxf(m_run, pair_max(mx));
-    const float alpha = exp2f(m_run - m_new);
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
     m_run = m_new;
     float l_tile = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = exp2f(s[r] - m_new);
+      s[r] = __builtin_amdgcn_exp2f(s[r] - m_new);
       l_tile += s[r];
     }
     l_run = l_run * alpha + l_tile;
@@ -230,7 +247,6 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
         }
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] = __builtin_fmaf(o[db][r], alpha, t[r] + t1[r]);
-        __builtin_amdgcn_sched_barrier(0);  // the next block's V reads stay behind: 256 VGPRs do not hold them too
       } else {
 #pragma unroll
         for (int r = 0; r < 16; ++r)
@@ -238,6 +254,7 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
 #pragma unroll
         for (int r = 0; r < 16; ++r) o[db][r] = __builtin_fmaf(o[db][r], alpha, t[r]);
       }
+      __builtin_amdgcn_sched_barrier(0);  // the next block's V reads stay behind: 256 VGPRs do not hold them too
     }
   };
 
@@ -360,10 +377,10 @@ __global__ __launch_bounds__(kCombThreads) void attend_f32_combine_kernel(Attend
 typedef void (*F32Kernel)(AttendArgs, int, int);
 typedef void (*F32Combine)(AttendArgs, int, int, int);
 
-// Bytes of entry tables a workgroup can hold beside its tiles (128 KB at
+// Bytes of entry table a workgroup can hold beside its tiles (128 KB at
 // D = 128): the largest memory, M + staged frames, fits.
-constexpr size_t kMaxTable = 16 * 1024;
-static_assert((kMaxBudget + kMaxPlanFrames) * 2 * sizeof(int32_t) <= kMaxTable, "entry tables fit");
+constexpr size_t kMaxTable = 20 * 1024;
+static_assert((kMaxBudget + kMaxPlanFrames + 1) * 2 * sizeof(const char*) <= kMaxTable, "entry table fits");
 
 // Key tiles times 32-query blocks of a call from which four query waves
 // share a tile (two splits, double-buffered) rather than two (four splits):
@@ -374,7 +391,7 @@ constexpr int64_t kWideFrom = 8192;
 
 hipError_t launch_f32(F32Kernel wide, F32Kernel narrow, F32Combine combine, std::once_flag& attr_once,
                       const AttendArgs& a, hipStream_t stream) {
-  const size_t shmem = size_t(a.n_entries) * 2 * sizeof(int32_t);  // entry tables; tile buffers are static
+  const size_t shmem = size_t(a.n_entries + 1) * 2 * sizeof(const char*);  // entry table; tile buffers are static
   if (shmem > kMaxTable) return hipErrorInvalidValue;
   const int64_t lk = a.n_entries * a.tokens_per_block + a.cur_tokens;
   const int n_tiles = int((lk + kTile - 1) / kTile);
