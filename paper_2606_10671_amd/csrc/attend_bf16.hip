@@ -168,20 +168,25 @@ __device__ __forceinline__ int xcd_group(int bid, int groups) {
   return (xcd < rem) ? xcd * (per + 1) + local : rem * (per + 1) + (xcd - rem) * per + local;
 }
 
-// One lane's part of 32-row block db of O^T (query q_row, head h), scaled by
-// inv, into its O row.
+// One lane's registers 4 g4 .. 4 g4 + 3 of 32-row block db of O^T (query
+// q_row, head h), o[0..3], scaled by inv, into its O row.
+template <int D>
+__device__ __forceinline__ void store_quad(const AttendArgs& args, const float* o, int db, int g4, float inv,
+                                           int q_row, int h, int hh) {
+  if (q_row >= int(args.q_tokens)) return;
+  char* obase = static_cast<char*>(args.out) + (size_t(q_row) * args.heads + h) * D * 2;
+  bf16x4 v;
+#pragma unroll
+  for (int r = 0; r < 4; ++r) v[r] = (__bf16)(o[r] * inv);
+  *reinterpret_cast<bf16x4*>(obase + (32 * db + 8 * g4 + 4 * hh) * 2) = v;
+}
 template <int D>
 __device__ __forceinline__ void store_block(const AttendArgs& args, const f32x16& o, int db, float inv, int q_row,
                                             int h, int hh) {
-  if (q_row >= int(args.q_tokens)) return;
-  char* obase = static_cast<char*>(args.out) + (size_t(q_row) * args.heads + h) * D * 2;
 #pragma unroll
   for (int g4 = 0; g4 < 4; ++g4) {
-    bf16x4 v;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = (__bf16)(o[4 * g4 + r] * inv);
-    const int d = 32 * db + 8 * g4 + 4 * hh;
-    *reinterpret_cast<bf16x4*>(obase + d * 2) = v;
+    const float q[4] = {o[4 * g4], o[4 * g4 + 1], o[4 * g4 + 2], o[4 * g4 + 3]};
+    store_quad<D>(args, q, db, g4, inv, q_row, h, hh);
   }
 }
 // The row's log-sum-exp, if asked for.
@@ -792,29 +797,32 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
 // Merge of split query tiles: block (i, w) combines the parts of remaining
 // tile i for the 32 queries of wave w, wave db of the block taking the
 // 32-row block db of O^T, and writes the output.  Bound by the latency of
-// reading the partials (from L2 and the Infinity Cache); eight small blocks
-// per tile fill the chip when few tiles are split (24 tiles of 2 parts 9.2 us
-// as one block per tile, 24 tiles of 10 parts 8.5 us so).  TWO: every tile
-// has two parts, whose loads are then all in flight at once.
+// reading the partials (from L2 and the Infinity Cache).  TWO: every tile has
+// two parts, whose loads are then all in flight at once.  Otherwise block
+// (i, w, z) takes a quarter of the registers, eight parts in flight: few
+// tiles of many parts then fill the chip (2 heads x 500 queries over 10500
+// keys, 22 parts: 31.0 us a call, 33.6 with whole blocks; 12 x 390 over 3900,
+// 10 parts: 26.4 and 27.4).
+constexpr int kMergeSplit = 4;  // 16 registers, 4 per block
 template <int D, bool TWO>
 __device__ __forceinline__ void attend_bf16_merge_body(const AttendArgs& args, const SkPlan& plan) {
   static_assert(QB == 1, "one 32-query block per wave");
   const int i = blockIdx.x, wave = blockIdx.y;
   const int qg = plan.rounds * plan.groups + i;
+  const int h = qg / plan.q_tiles;
   const int db = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
   const int hh = lane >> 5;
-  const int q0 = (qg % plan.q_tiles) * kBM + wave * kQW;
+  const int q0 = (qg % plan.q_tiles) * kBM + wave * kQW, q_row = q0 + (lane & 31);
   if (q0 >= int(args.q_tokens)) return;  // the wave left no result
   const float c2 = args.scale * kLog2e;
   const int mi = kBM * D + wave * 64 + lane, li = mi + kThreads;
   const float* base = args.ws + size_t(i) * attend_slot_floats(D);
   const size_t step = size_t(plan.rem) * attend_slot_floats(D);  // from one part of the tile to its next
-  f32x16 o;
   float m_max, l_tot;
   if constexpr (TWO) {
     const float* other = base + step;
-    f32x16 o1;
+    f32x16 o, o1;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       o[r] = base[ws_o_index<D>(wave, 0, db, r, lane)];
@@ -826,25 +834,27 @@ __device__ __forceinline__ void attend_bf16_merge_body(const AttendArgs& args, c
     l_tot = f0 * pair_sum(base[li]) + f1 * pair_sum(other[li]);
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[r] = f0 * o[r] + f1 * o1[r];
+    store_block<D>(args, o, db, 1.0f / l_tot, q_row, h, hh);
+    if (db == 0) store_lse(args, m_max * c2, l_tot, q_row, h, hh);
   } else {
     const int parts = plan.heads_per + (plan.tail_len > 0 ? 1 : 0);
+    const int z = blockIdx.z;
     m_max = base[mi];
-#pragma unroll 4
+#pragma unroll 8
     for (int p = 1; p < parts; ++p) m_max = fmaxf(m_max, base[p * step + mi]);
-#pragma unroll
-    for (int r = 0; r < 16; ++r) o[r] = 0.0f;
+    float o[4] = {0.0f, 0.0f, 0.0f, 0.0f};
     l_tot = 0.0f;
-#pragma unroll 4
+#pragma unroll 8
     for (int p = 0; p < parts; ++p) {
       const float* ws = base + p * step;
       const float f = __builtin_amdgcn_exp2f((ws[mi] - m_max) * c2);
       l_tot += f * pair_sum(ws[li]);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[r] += f * ws[ws_o_index<D>(wave, 0, db, r, lane)];
+      for (int r = 0; r < 4; ++r) o[r] += f * ws[ws_o_index<D>(wave, 0, db, 4 * z + r, lane)];
     }
+    store_quad<D>(args, o, db, z, 1.0f / l_tot, q_row, h, hh);
+    if (db == 0 && z == 0) store_lse(args, m_max * c2, l_tot, q_row, h, hh);
   }
-  store_block<D>(args, o, db, 1.0f / l_tot, q0 + (lane & 31), qg / plan.q_tiles, hh);
-  if (db == 0) store_lse(args, m_max * c2, l_tot, q0 + (lane & 31), qg / plan.q_tiles, hh);
 }
 
 }  // namespace
@@ -935,8 +945,8 @@ hipError_t launch_d(AttnKernel kernel, AttnKernel merge2, AttnKernel merge_n, st
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int parts = plan.heads_per + (plan.tail_len > 0 ? 1 : 0);
   if (plan.rem > 0 && parts > 1) {
-    hipLaunchKernelGGL(parts == 2 ? merge2 : merge_n, dim3(plan.rem, kWaves), dim3(2 * a.head_dim), 0, stream, a,
-                       plan);
+    hipLaunchKernelGGL(parts == 2 ? merge2 : merge_n, dim3(plan.rem, kWaves, parts == 2 ? 1 : kMergeSplit),
+                       dim3(2 * a.head_dim), 0, stream, a, plan);
     e = hipGetLastError();
   }
   return e;
