@@ -54,14 +54,14 @@ struct SpecLayout {
   size_t off_ah, off_aw, off_d, off_perm, off_start, off_clip, total;
 };
 
-bool spec_layout(int64_t clips, int64_t nlag, int64_t H, int64_t W, int64_t bands, bool fused, SpecLayout* L) {
-  const double d_bytes = fused ? 0.0 : double(clips) * double(nlag) * double(H) * double(W) * 4.0;
+bool spec_layout(int64_t clips, int64_t nlag, int64_t H, int64_t W, int64_t bands, bool on_chip, SpecLayout* L) {
+  const double d_bytes = on_chip ? 0.0 : double(clips) * double(nlag) * double(H) * double(W) * 4.0;
   const double c_bytes = double(clips) * double(nlag) * double(bands) * 24.0;
   if (d_bytes > 1e15 || c_bytes > 1e15) return false;
   size_t off = 0;
   L->off_ah = off;    off = rup(off + size_t(H * H) * 4);
   L->off_aw = off;    off = rup(off + size_t(W * W) * 4);
-  L->off_d = off;     off = rup(off + (fused ? 0 : size_t(clips) * size_t(nlag) * size_t(H * W) * 4));
+  L->off_d = off;     off = rup(off + (on_chip ? 0 : size_t(clips) * size_t(nlag) * size_t(H * W) * 4));
   L->off_perm = off;  off = rup(off + size_t(H * W) * 4);
   L->off_start = off; off = rup(off + size_t(bands + 1) * 4);
   L->off_clip = off;  off = rup(off + size_t(clips) * size_t(nlag) * size_t(bands) * 24);
