@@ -55,20 +55,20 @@ FP32_MFMA_PEAK_TFLOPS = 157.3  # dense fp32 matrix-core peak (same figure as the
 
 # HBM bytes of one steady-state bf16 attention call (main kernel + merge of
 # split tiles) at the wan1.3b-1layer workload, from rocprofv3 FETCH_SIZE and
-# WRITE_SIZE (see profiles/attend_bf16_wan1.3b_1layer.md), valid only for the
+# WRITE_SIZE (see profiles/perf_cases.md), valid only for the
 # kernel source they were taken on (first 16 hex digits of its sha256).
-ATTN_TRAFFIC = {"source_sha256": "a3f76e85dfec4181", "workload": "wan1.3b-1layer", "bytes_per_call": 1034552248}
+ATTN_TRAFFIC = {"source_sha256": "b43f8c9f815a8568", "workload": "wan1.3b-1layer", "bytes_per_call": 965072016}
 
 
 # HBM bytes of one fused chunk update's data pass (update_data_kernel) in
 # the 30-layer update leg, from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled
-# by the insert copy (see profiles/update_data_wan1.3b_30layer.md); valid
+# by the insert copy (see profiles/perf_cases.md); valid
 # only for the cache.hip source they were taken on.
-UPD_TRAFFIC = {"source_sha256": "15da6713f8357ab0", "workload": "wan1.3b-30layer-update", "bytes_per_call": 4259822800}
+UPD_TRAFFIC = {"source_sha256": "d8676615def3670d", "workload": "wan1.3b-30layer-update", "bytes_per_call": 4259836436}
 
 # HBM bytes of one spectral analysis call (all its kernels) at spectral-374clips, from rocprofv3 FETCH_SIZE and
-# WRITE_SIZE scaled by the insert copy (see profiles/spectral_fused_374clips.md); valid only for this source.
-SPEC_TRAFFIC = {"source_sha256": "cdbe5ca3b4bd15d7", "workload": "spectral-374clips", "bytes_per_call": 1740286899}
+# WRITE_SIZE scaled by the insert copy (see profiles/perf_cases.md); valid only for this source.
+SPEC_TRAFFIC = {"source_sha256": "5a5b9dbaf38bcf74", "workload": "spectral-374clips", "bytes_per_call": 1755505004}
 
 
 def measured_traffic(table, source, workload):
