@@ -57,7 +57,7 @@ FP32_MFMA_PEAK_TFLOPS = 157.3  # dense fp32 matrix-core peak (same figure as the
 # split tiles) at the wan1.3b-1layer workload, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE (see profiles/perf_cases.md), valid only for the
 # kernel source they were taken on (first 16 hex digits of its sha256).
-ATTN_TRAFFIC = {"source_sha256": "b43f8c9f815a8568", "workload": "wan1.3b-1layer", "bytes_per_call": 965072016}
+ATTN_TRAFFIC = {"source_sha256": "34b8fc2e8b08b740", "workload": "wan1.3b-1layer", "bytes_per_call": 965455936}
 
 
 # HBM bytes of one fused chunk update's data pass (update_data_kernel) in
