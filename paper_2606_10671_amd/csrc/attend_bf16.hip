@@ -320,16 +320,20 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
         qf[qb][kb] = *reinterpret_cast<const bf16x8*>(qbase + (16 * kb + 8 * hh) * 2);
     }
 
-    // Address of the last key's row (rows past the last key load it again).
+    // Address of the last key's row (rows past the last key load it again),
+    // from the entry table: only after a barrier.
     const char* last_k;
     long long last_vd;
-    if (cur_tokens > 0) {
-      last_k = k_cur + size_t(cur_tokens - 1) * row_bytes + head_off;
-      last_vd = ent_vd[n_entries];
-    } else {
-      last_k = ent_k[n_entries - 1] + size_t(N - 1) * row_bytes + head_off;
-      last_vd = ent_vd[n_entries - 1];
-    }
+    auto enter = [&] {
+      __syncthreads();  // entry table visible; the previous segment's reads of the buffers are done
+      if (cur_tokens > 0) {
+        last_k = k_cur + size_t(cur_tokens - 1) * row_bytes + head_off;
+        last_vd = ent_vd[n_entries];
+      } else {
+        last_k = ent_k[n_entries - 1] + size_t(N - 1) * row_bytes + head_off;
+        last_vd = ent_vd[n_entries - 1];
+      }
+    };
 
     // Load stream: the next tile to load starts in entry ld_e at row ld_off
     // (ld_e == n_entries: the current chunk).
@@ -429,7 +433,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
     // of every tile's loads and meets the same barriers as the other waves
     // (two in the prologue, one per key tile), and leaves no result.
     if (qt * kBM + wave * kQW >= Lq) {
-      __syncthreads();
+      enter();
       issue_tile(kt0, kbuf[0], vbuf[0]);
       if (kt0 + 1 < kt1) issue_tile(kt0 + 1, kbuf[1], vbuf[1]);
       __builtin_amdgcn_s_waitcnt(0);
@@ -704,7 +708,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
 
     // Prologue: tiles kt0 and kt0+1 into ring slots 0 and 1; S(kt0), its
     // exact row max and its first kPairsB weights.
-    __syncthreads();  // entry table visible; the previous segment's reads of the buffers are done
+    enter();
     issue_tile(kt0, kbuf[0], vbuf[0]);
     if (kt0 + 1 < kt1) issue_tile(kt0 + 1, kbuf[1], vbuf[1]);
     __builtin_amdgcn_s_waitcnt(0);
