@@ -85,6 +85,7 @@ struct SkPlan {
   int head_len;   // key tiles of a remaining tile's head parts together
   int tail_len;   // key tiles of its tail part (0: no tail)
   int tails_per;  // tails per tail group
+  float seed;     // of the remaining tiles' segments: 0, or (unsplit) for exact row maxima
 };
 
 namespace {
@@ -107,7 +108,7 @@ constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescaleBound = 256.0f;  // redo a tile whose weights exceed 2^8
 constexpr int kSegOverhead = 2;          // key tiles' worth of time a segment's prologue and epilogue cost
-constexpr int kMinSplit = 6;             // key tiles a query tile needs to be split at all
+constexpr int kMinSplit = 6;             // key tiles a query tile needs to be split at all (two parts)
 constexpr int kMinPart = 6;              // key tiles of a head part at least
 constexpr int kMinTailSaves = 2;         // key tiles a tail has to take off each head part
 constexpr int kMaxParts = 64;            // head parts of a query tile at most
@@ -304,9 +305,12 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
 
   // One query tile's key tiles [kt0, kt1); the result goes to the output
   // (slot < 0, the range is the whole key axis) or, partial, to scratch slot
-  // `slot`.
-  auto segment = [&](int h, int qt, int kt0, int kt1, int slot) {
+  // `slot`.  seed: 0, or 2 kRescaleBound + a fall allowed to m_run: the weight
+  // sums of the tiles after the first start from it, so that each is redone
+  // against its exact max.
+  auto segment = [&](int h, int qt, int kt0, int kt1, int slot, float seed) {
     const size_t head_off = size_t(h) * D * 2;
+    asm volatile("" : "+v"(seed));  // in a VGPR: scalar ones run out, and a spilled one costs a lane read per tile
 
     // Q fragments (B operand of S^T = K Q^T): query m = l32 of block qb,
     // d = 16*kb + 8*hh + 0..7.
@@ -540,15 +544,18 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
     };
     // Redo a tile against the exact running max: its scores again from its K
     // buffer, new m_run, rescale O and l, recompute all its weights and the
-    // tile sum.
+    // tile sum.  With a seed m_run may also fall, to the tile's own max, so
+    // that each tile's largest weight is 1 as in a part of its own, but by 2^8
+    // at most over the whole segment (the headroom a stale max has).
     auto redo_tile = [&](int tile, const char* kb_lds, u32x4 (&p)[4][QB], float (&ps)[QB]) {
       f32x16 s[2][QB];
       qk_tile(tile, kb_lds, s);
       float mx[QB];
       row_max(s, mx);
+      const float fall = __builtin_elementwise_maximum(seed - 2.0f * kRescaleBound, 0.0f);
 #pragma unroll
       for (int qb = 0; qb < QB; ++qb) {
-        const float m_new = __builtin_elementwise_maximum(m_run[qb], mx[qb]);
+        const float m_new = __builtin_elementwise_maximum(m_run[qb] - fall, mx[qb]);
         const float alpha = __builtin_amdgcn_exp2f((m_run[qb] - m_new) * c2);
         m_run[qb] = m_new;
         l_run[qb] *= alpha;
@@ -668,7 +675,7 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
       u32x4 p_next[4][QB];
       float ps_next[QB];
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) ps_next[qb] = 0.0f;
+      for (int qb = 0; qb < QB; ++qb) ps_next[qb] = seed;
 #pragma unroll
       for (int st = 0; st < kStepsB; ++st) {
         const int ks = st / (S::DB / kDbPerStep), db0 = (st % (S::DB / kDbPerStep)) * kDbPerStep;
@@ -797,7 +804,8 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
       kt0 = plan.head_len;
       slot = head_groups + i;
     }
-    segment(qg / plan.q_tiles, qg % plan.q_tiles, kt0, kt1, slot);
+    segment(qg / plan.q_tiles, qg % plan.q_tiles, kt0, kt1, slot,
+            part >= plan.rounds ? plan.seed : 0.0f);
   }
 }
 
@@ -918,7 +926,8 @@ hipError_t launch_d(AttnKernel kernel, AttnKernel merge2, AttnKernel merge_n, st
   plan.heads_per = 1;
   plan.tails_per = 1;
   plan.tail_len = 0;
-  if (plan.rem > 0 && plan.tiles >= kMinSplit) {
+  plan.seed = 0.0f;
+  if (plan.rem > 0) {
     // Splitting pays once the key tiles it saves outweigh the merge launch
     // (about 5 us, a key tile 1.2-1.8 us).  Head parts: as many as the groups
     // allow, none shorter than kMinPart tiles (one segment costs 10-13 us
@@ -935,12 +944,24 @@ hipError_t launch_d(AttnKernel kernel, AttnKernel merge2, AttnKernel merge_n, st
     // Tails that take less than two tiles off every head part are not worth
     // their slots: 12 heads x 1170 queries over 92 tiles (16 groups left for
     // 60 tails) 53.5 us without tails, 59.6 us with.
+    int len = 0;
     const int left = plan.groups - plan.heads_per * plan.rem;
     if (left > 0) {
       plan.tails_per = (plan.rem + left - 1) / left;
       const int over = kSegOverhead * (plan.tails_per - 1) * plan.heads_per;
-      const int len = plan.tiles > over ? (plan.tiles - over) / (plan.tails_per * plan.heads_per + 1) : 0;
-      if (len >= kMinTailSaves * plan.heads_per) plan.tail_len = len;
+      len = plan.tiles > over ? (plan.tiles - over) / (plan.tails_per * plan.heads_per + 1) : 0;
+    }
+    if (plan.tiles >= kMinSplit && len >= kMinTailSaves * plan.heads_per) {
+      plan.tail_len = len;
+    } else if (plan.heads_per == 1 && len > 0) {
+      // A tile that could have a second part, but is not worth it, runs every
+      // key tile with its exact row max instead: against a stale max a row's
+      // largest weight is some 2^x, x <= 8, rounded to bf16, while in a part's
+      // first tile it is 1.  24 x 128 heads, 256 queries, 4 tiles: 17.9 us and
+      // error 2.10e-3 so, 24.5 us and 2.23e-3 in two parts, 14.8 us and
+      // 2.29e-3 in one with a stale max.  From kMinSplit tiles two parts cost
+      // less (24 x 64, 5 tiles: 14.2 us so, 14.1 in two parts).
+      plan.seed = 2.0f * kRescaleBound + 8.0f / (float(plan.tiles - 1) * a.scale * kLog2e);
     }
   }
   plan.head_len = plan.tiles - plan.tail_len;
