@@ -724,7 +724,12 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
       qk_tile(kt0, kbuf[0], s_cur);
       row_max(s_cur, m_run);
 #pragma unroll
-      for (int qb = 0; qb < QB; ++qb) ps_cur[qb] = 0.0f;
+      for (int qb = 0; qb < QB; ++qb) {
+        // Every score -inf: weights 0 against a finite max below any other
+        // score (against -inf they would be NaN), which the next tile redoes.
+        if (m_run[qb] == -INFINITY) m_run[qb] = -1e30f;
+        ps_cur[qb] = 0.0f;
+      }
 #pragma unroll
       for (int pi = 0; pi < kPairsB; ++pi) exp_pair(s_cur, p_cur, ps_cur, pi);
     }
