@@ -219,12 +219,13 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     const float m_new = fmaxf(m_run, pair_max(mx));
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_new);
+    const float m_ref = m_new == -INFINITY ? 0.0f : m_new;  // every score -inf so far: weights 0, not NaN
+    const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
     m_run = m_new;
     float l_tile = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f(s[r] - m_new);
+      s[r] = __builtin_amdgcn_exp2f(s[r] - m_ref);
       l_tile += s[r];
     }
     l_run = l_run * alpha + l_tile;

@@ -41,3 +41,13 @@ def rows(tiles, size=64):
 ])
 def test_bf16_masked_tiles(H, D, q_tokens, keys, tiles):
     check("bf16", H, D, q_tokens, keys, rows(tiles))
+
+
+@pytest.mark.parametrize("H,D,q_tokens,keys,tiles", [
+    (2, 64, 40, 8 * 32, [0, 1, 2, 3]),                 # every split's first tile
+    (1, 128, 40, 40 * 32, range(0, 40, 2)),            # whole splits, ranges combined by the second kernel
+    (12, 128, 300, 101 * 32 + 7, [0, 1, 2, 50, 51]),   # four query waves, two splits
+    (2, 64, 33, 64, [0]),
+])
+def test_f32_masked_tiles(H, D, q_tokens, keys, tiles):
+    check("f32", H, D, q_tokens, keys, rows(tiles, 32))
