@@ -220,14 +220,25 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
     const float m_new = fmaxf(m_run, pair_max(mx));
     const float m_ref = m_new == -INFINITY ? 0.0f : m_new;  // every score -inf so far: weights 0, not NaN
-    const float alpha = __builtin_amdgcn_exp2f(m_run - m_ref);
+    const float alpha = exp2f(m_run - m_ref);
     m_run = m_new;
-    float l_tile = 0.0f;
+    float least = 0.0f, l_tile = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] = __builtin_amdgcn_exp2f(s[r] - m_ref);
-      l_tile += s[r];
+      s[r] -= m_ref;
+      least = fminf(least, s[r]);
     }
+    // The instruction alone makes weights below 2^-126 zero, exp2f does not: it
+    // is taken for the tiles that hold such weights.
+    if (__any(least < -126.0f)) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = exp2f(s[r]);
+    } else {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s[r] = __builtin_amdgcn_exp2f(s[r]);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) l_tile += s[r];
     l_run = l_run * alpha + l_tile;
     // The tile's own O^T, one block at a time, from zero, then added to the
     // running one: its 32 keys round at the tile's size, not at the whole
