@@ -124,13 +124,16 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
     rows_s[2 * e + 1] = vr + head_off;
   }
 
-  // Query l32, elements 8 j + 4 hh + e, in the log2 domain.
+  // Query l32, elements 8 j + 4 hh + e, times the power of two in the scale (in
+  // the log2 domain), which rounds nothing; the rest of it, c in [1, 2), enters
+  // where a score's distance to the row max is taken, in one rounding.
   const float c2 = args.scale * kLog2e;
+  const float cp = fmaxf(__uint_as_float(__float_as_uint(c2) & 0x7f800000u), 0x1p-126f), c = c2 / cp;
   f32x4 q[D / 8];
   {
     const char* qp = static_cast<const char*>(args.q) + size_t(q_row < Lq ? q_row : Lq - 1) * row_bytes + head_off;
 #pragma unroll
-    for (int j = 0; j < D / 8; ++j) q[j] = *reinterpret_cast<const f32x4*>(qp + 32 * j + 16 * hh) * c2;
+    for (int j = 0; j < D / 8; ++j) q[j] = *reinterpret_cast<const f32x4*>(qp + 32 * j + 16 * hh) * cp;
   }
   f32x16 o[DB];
 #pragma unroll
@@ -218,14 +221,14 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
     float mx = s[0];
 #pragma unroll
     for (int r = 1; r < 16; ++r) mx = fmaxf(mx, s[r]);
-    const float m_new = fmaxf(m_run, pair_max(mx));
+    const float m_new = fmaxf(m_run, pair_max(mx) * c);
     const float m_ref = m_new == -INFINITY ? 0.0f : m_new;  // every score -inf so far: weights 0, not NaN
     const float alpha = exp2f(m_run - m_ref);
     m_run = m_new;
     float least = 0.0f, l_tile = 0.0f;
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      s[r] -= m_ref;
+      s[r] = __builtin_fmaf(s[r], c, -m_ref);
       least = fminf(least, s[r]);
     }
     // The instruction alone makes weights below 2^-126 zero, exp2f does not: it

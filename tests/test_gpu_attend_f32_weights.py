@@ -1,5 +1,6 @@
 """The softmax weights of fp32 attention at the ends of their range: weights
-below 2^-126, fp32's smallest normal number, still count."""
+below 2^-126, fp32's smallest normal number, still count; and scores that are
+small against their terms: the scale is not rounded into the products."""
 import numpy as np
 import pytest
 
@@ -41,3 +42,21 @@ def test_subnormal_rescale(H, D, q_tokens, keys):
     O, _ = run(H, D, q, k, v)
     assert np.isposinf(O[..., 3]).all()
     assert np.abs(O[..., 0] - 1.0).max() <= 1e-6
+
+
+@pytest.mark.parametrize("H,D,q_tokens,keys", SHAPES)
+def test_scores_that_fp32_holds_are_not_rounded(H, D, q_tokens, keys):
+    """Scores that are small sums of large products, all exact in fp32 (x 2^20 - x 2^20 + a whole number):
+    the scale, which fp32 does not hold, must not be rounded into the products.  Rounded into q it is off by up to
+    2^-24 of 0.18 x 2^20 there, differently for q = 1 and q = x, and moves weights by about 1%."""
+    rng = np.random.default_rng(keys)
+    q, k = np.zeros((q_tokens, H, D), np.float32), np.zeros((keys, H, D), np.float32)
+    v = rng.standard_normal((keys, H, D)).astype(np.float32)
+    large = rng.choice([-1.0, 0.0, 1.0], (keys, H)).astype(np.float32) * 2.0 ** 20
+    k[..., 0], k[..., 4] = large, rng.integers(0, 32, (keys, H))
+    q[..., 2], q[..., 4] = 1.0, 1.0
+    for x in (3, 5, 7):
+        q[..., 0], k[..., 2] = x, -x * large
+        O, L = run(H, D, q, k, v)
+        O_ref, L_ref = attend(q, [], [], k, v)
+        check_attention(O, L, O_ref, L_ref, "f32", (x, H, D, q_tokens, keys))
