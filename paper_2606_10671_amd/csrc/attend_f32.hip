@@ -418,14 +418,18 @@ hipError_t launch_f32(F32Kernel wide, F32Kernel narrow, F32Combine combine, std:
   const int total = q_tiles * a.heads;
   const int most = std::min<int64_t>(f32_ws_bytes(a.head_dim) / sizeof(float) / part_floats(qt_rows, a.head_dim) / total,
                                      (n_tiles + KS - 1) / KS);
-  // Key ranges: as many as finish first, in rounds of one workgroup per CU,
-  // a key tile of a split counting 4, a workgroup's start and end 6 and the
-  // combine 6; as many as the slots hold, and a tile for every split.
+  // Key ranges: as many as finish first, up to a tile for every split and the
+  // slots there are, in rounds of one workgroup per CU.  In units of 70 ns, a
+  // key tile of a split takes D, a workgroup's start and end 128, the combine
+  // 40 and, as few workgroups wait for one slot after another, 9 per range
+  // (measured: 8.7 us a tile and 0.65 us a range at D = 128, 4.7 and 0.62 at
+  // D = 64).  So one head of 128 queries over 65536 keys takes 128 ranges, 164
+  // us (64 ranges 192, 256 ranges 212).
   int parts = 1;
   int64_t best = INT64_MAX;
-  for (int p = 1; p <= std::max(1, std::min(most, 64)); ++p) {
-    const int64_t rounds = (int64_t(total) * p + 255) / 256, per = (n_tiles + p * KS - 1) / (p * KS);
-    const int64_t cost = rounds * (per * 4 + 6) + (p > 1 ? 6 : 0);
+  for (int p = 1; p <= std::max(1, most) && 9 * p < best; ++p) {
+    const int rounds = int((int64_t(total) * p + 255) / 256), per = (n_tiles + p * KS - 1) / (p * KS);
+    const int64_t cost = int64_t(rounds) * (int64_t(per) * a.head_dim + 128) + (p > 1 ? 40 + 9 * p : 0);
     if (cost < best) {
       best = cost;
       parts = p;
