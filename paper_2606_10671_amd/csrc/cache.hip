@@ -730,6 +730,10 @@ __global__ __launch_bounds__(256) void update_plan_small_kernel(PlanArgs a) {
     }
     n -= 1;
   }
+  // Lane 0's writes to free_s and ws_s, before the other lanes' reads of them
+  // (wave 0 alone is left, so no block barrier).
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
 
   // Slots: kept old entries stay; every new or changed entry takes a free
   // slot (those free before, or freed by this update), in order.
