@@ -50,8 +50,7 @@ SPECTRAL = {"spectral-374clips": dict(clips=374, frames=177, height=60, width=10
 
 HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
-FP32_VECTOR_PEAK_TFLOPS = 157.3
-FP32_MFMA_PEAK_TFLOPS = 157.3  # dense fp32 matrix-core peak (same figure as the vector peak)
+FP32_MFMA_PEAK_TFLOPS = 157.3  # dense fp32 matrix-core peak
 
 # HBM bytes of one steady-state bf16 attention call (main kernel + merge of
 # split tiles) at the wan1.3b-1layer workload, from rocprofv3 FETCH_SIZE and
@@ -89,6 +88,11 @@ def measured_traffic(table, source, workload):
 def attn_traffic(workload):
     """Measured HBM bytes per attention call (None: source or workload differ)."""
     return measured_traffic(ATTN_TRAFFIC, "attend_bf16.hip", workload)
+
+
+def plan_kernel(budget):
+    """The kernel that plans a fused update: one lane per entry where the memory fits a wave."""
+    return "update_plan_small_kernel" if budget + 1 <= 64 else "update_plan_kernel"
 
 
 def parse():
@@ -332,7 +336,7 @@ def update_leg(args, M, anchor, L=30, H=12, D=128, N=1560, F=3):
     torch.cuda.empty_cache()
     fused = modes["fused"]
     traffic = measured_traffic(UPD_TRAFFIC, "cache.hip", "wan1.3b-30layer-update") if M == 21 else None
-    roof = {"bound": "hbm", "kernel": f"update_plan_kernel + update_data_kernel (one fademem_update call, {L} layers)",
+    roof = {"bound": "hbm", "kernel": f"{plan_kernel(M)} + update_data_kernel (one fademem_update call, {L} layers)",
             "achieved": fused["gbps"], "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(fused["gbps"] / HBM_PEAK_GBS, 4) if fused["gbps"] else None,
             "traffic": traffic, "traffic_unit": "bytes per call (HBM read + write)",
@@ -531,7 +535,7 @@ def main():
     state = cache_timed.state()
     peak_bytes = cache_timed.pool_bytes
     is_bf16 = tdtype == torch.bfloat16
-    peak = MFMA_BF16_PEAK_TFLOPS if is_bf16 else FP32_VECTOR_PEAK_TFLOPS
+    peak = MFMA_BF16_PEAK_TFLOPS if is_bf16 else FP32_MFMA_PEAK_TFLOPS
     result = {
         "metric": "ms per generated chunk (merge+attend), attention TFLOP/s, merge GB/s",
         "value": round(ms_chunk, 4),
@@ -572,7 +576,7 @@ def main():
         "pool_bytes": peak_bytes,
         "final_spans": state["span"],
         "roofline": {
-            "bound": "mfma" if is_bf16 else "alu",
+            "bound": "mfma",
             "kernel": ("attend_bf16_d128 + attend_bf16_merge<128> (one attend call)" if D == 128 else
                        "attend_bf16_d64 + attend_bf16_merge<64> (one attend call)") if is_bf16
                       else "attend_f32_kernel + attend_f32_combine_kernel (one attend call)",
@@ -609,7 +613,7 @@ def main():
             result["merge_roofline"], result["update_leg"] = update_leg(args, M, anchor)
         elif update_gbps:
             result["merge_roofline"] = {
-                "bound": "hbm", "kernel": f"update_plan_kernel + update_data_kernel (one fademem_update call, {L} layers)",
+                "bound": "hbm", "kernel": f"{plan_kernel(M)} + update_data_kernel (one fademem_update call, {L} layers)",
                 "achieved": round(update_gbps, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                 "frac": round(update_gbps / HBM_PEAK_GBS, 4), "traffic": None,
                 "traffic_unit": "bytes per call (HBM read + write)", "workload": args.workload}

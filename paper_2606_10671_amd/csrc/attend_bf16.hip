@@ -600,8 +600,9 @@ __device__ __forceinline__ void attend_bf16_body(const AttendArgs& args, const S
     constexpr int kStepsB = 2 * S::DB;                // block B steps: (ks, pair of 32-row blocks)
     constexpr int kDbPerStep = S::DB * 4 / kStepsB;   // = 2
     // Steps between an LDS read and its MFMA.  At D = 64 there are registers
-    // for two, and half the MFMAs to cover a read: 16 heads x 2002 queries over
-    // 17017 keys 154.7 us, 155.8 with one; 24 x 4680 over 37440 1170 and 1180.
+    // for two, and half the MFMAs to cover a read: 24 heads x 4680 queries over
+    // 37440 keys 1130-1133 us, 1146-1148 with one; 16 x 2002 over 17017 157.3
+    // and 158.5; shorter calls the same (three alternating runs each).
     constexpr int kPrefetch = D == 64 ? 2 : 1;
 
     // One pipeline iteration for tile t: boundary, block A, tile t's weight

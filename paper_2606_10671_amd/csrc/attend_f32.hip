@@ -32,9 +32,9 @@
 // Bound by the matrix cores (a tile of 32 keys x 32 queries is 2 x 64 MFMAs
 // of 64 cycles at D = 128) and, since fp32 matrix instructions do not run
 // beside vector ones on a SIMD, by the vector work of the softmax and the
-// loads' addresses: 12 heads x 1170 queries over 5850 keys take 418 us (100
-// TFLOP/s of the 157 peak; 1137 us on the vector ALUs with K/V broadcast from
-// LDS), and the error against 64 bits falls from 3.1e-7 to 1.6e-7.
+// loads' addresses: 12 heads x 1170 queries over 5850 keys take 420-425 us (99
+// TFLOP/s of the 157 peak; 1100-1140 us on the vector ALUs with K/V broadcast
+// from LDS), and the error against 64 bits falls from 3.1e-7 to 1.6e-7.
 #include <algorithm>
 #include <mutex>
 
@@ -232,7 +232,8 @@ __global__ __launch_bounds__(kThreads, 2) void attend_f32_kernel(AttendArgs args
       least = fminf(least, s[r]);
     }
     // The instruction alone makes weights below 2^-126 zero, exp2f does not: it
-    // is taken for the tiles that hold such weights.
+    // is taken for the tiles that hold such weights (the test for them costs 1%
+    // of a long call at D = 128, 2% at D = 64).
     if (__any(least < -126.0f)) {
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = exp2f(s[r]);

@@ -389,6 +389,12 @@ __device__ __forceinline__ double wave_total3(double a, double b, double c) {
 // KB of LDS, 128 VGPRs) hide of the waits.  That call: 1.15 ms, 2.15 ms with
 // unfolded products, frames in pairs and one workgroup per CU; 48 x 61 frames
 // of 72 x 128: 131 us, 667 us through the general path.
+//
+// Registers: HT <= 2 is held to 128 VGPRs for two workgroups per CU.  <2, 3>
+// spills 2 of them and <2, 4> (61 to 64 folded columns) 15, also at heights
+// whose LDS admits one workgroup only (from 46 rows at 128 columns); <4, 3> and
+// <4, 4> spill 10 and 13 of 256.  96 x 61 frames of 64 x 128 take 159 us, 263 us
+// with unfolded products.
 template <int HT, int NQ>
 __global__ __launch_bounds__(kFusedThreads, HT <= 2 ? 4 : 2) void spectral_fused_kernel(
     const float* latents, int64_t frames, int nlag, int64_t clips, int H, int W, const float* AH, const float* AW,
