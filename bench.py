@@ -56,18 +56,18 @@ FP32_MFMA_PEAK_TFLOPS = 157.3  # dense fp32 matrix-core peak
 # split tiles) at the wan1.3b-1layer workload, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE (see profiles/perf_cases.md), valid only for the
 # kernel source they were taken on (first 16 hex digits of its sha256).
-ATTN_TRAFFIC = {"source_sha256": "34b8fc2e8b08b740", "workload": "wan1.3b-1layer", "bytes_per_call": 965455936}
+ATTN_TRAFFIC = {"source_sha256": "b1f732980ef42d52", "workload": "wan1.3b-1layer", "bytes_per_call": 966115584}
 
 
 # HBM bytes of one fused chunk update's data pass (update_data_kernel) in
 # the 30-layer update leg, from rocprofv3 FETCH_SIZE and WRITE_SIZE scaled
 # by the insert copy (see profiles/perf_cases.md); valid
 # only for the cache.hip source they were taken on.
-UPD_TRAFFIC = {"source_sha256": "d8676615def3670d", "workload": "wan1.3b-30layer-update", "bytes_per_call": 4259836436}
+UPD_TRAFFIC = {"source_sha256": "90913cfbf3c0ac10", "workload": "wan1.3b-30layer-update", "bytes_per_call": 4259831160}
 
 # HBM bytes of one spectral analysis call (all its kernels) at spectral-374clips, from rocprofv3 FETCH_SIZE and
 # WRITE_SIZE scaled by the insert copy (see profiles/perf_cases.md); valid only for this source.
-SPEC_TRAFFIC = {"source_sha256": "5a5b9dbaf38bcf74", "workload": "spectral-374clips", "bytes_per_call": 1755505004}
+SPEC_TRAFFIC = {"source_sha256": "89c004d91370a806", "workload": "spectral-374clips", "bytes_per_call": 1755538130}
 
 
 def measured_traffic(table, source, workload):
